@@ -1,14 +1,12 @@
 // surrogate_host.hip -- host side of the surrogate C ABI (include/surrogate.h):
-// workspace layout, weight packing, and the launch sequence of the forward
-// pass, the training step (loss, one backward kernel per layer for the input
-// and weight gradients, Adam with re-quantisation) and the conversion to
-// warm-start densities.
+// workspace layout, weight packing, the forward pass into the caller's output
+// (one launch) and the launch sequence of the training step (forward layers,
+// loss, one backward kernel per layer for the input and weight gradients, Adam
+// with re-quantisation).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
-#include <algorithm>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -31,12 +29,10 @@ hipError_t surx_reduce_adam(const float *part, const float *pbias, int P, float 
                             float c2, hipStream_t s);
 hipError_t surx_requant(const float *wm, __bf16 *Wf, __bf16 *Wb, int cin, int coutp, int cout_real, int kp, int kpb,
                         hipStream_t s);
-hipError_t surx_to_state(const float *out, const float *params, const double *n0, double *state, int X, int B,
-                         hipStream_t s);
 hipError_t surx_init_weights(float *wm, int cin, int coutp, int cout_real, int kp, uint32_t layer, uint32_t seed,
                              hipStream_t s);
-hipError_t surx_to_densities(const float *out, const double *n0, double *dens, int X, int B, hipStream_t s);
-hipError_t surx_unpack(const float *y, float *out, int X, int B, hipStream_t s);
+hipError_t surx_net(const __bf16 *const *wf, const float *const *bias, int mode, const float *params,
+                    const double *n0, void *out, int X, int B, hipStream_t s);
 }
 
 namespace {
@@ -67,7 +63,7 @@ struct Layer {
     int cin, cout, coutp, kp, kpb;
     float *wm, *mw, *vw, *dw;     // [coutp][kp] FP32 (kappa = t*cin + ci)
     float *bias, *mb, *vb, *db;   // [coutp]
-    __bf16 *wf;                   // [coutp][kp]
+    __bf16 *wf;                   // [coutp][kp] in fragment order
     __bf16 *wb;                   // [cin][kpb] (t*coutp + co)
 };
 
@@ -89,7 +85,6 @@ struct Bump {
 struct sur_net {
     int X = 0, bmax = 0;
     int device = -1;              // the GPU current at sur_create
-    char *scratch = nullptr;      // that GPU's copy of the allocation-free forward's scratch array
     hipStream_t stream = nullptr;
     char *ws = nullptr;
     size_t param_bytes = 0;       // weights, moments, grads: the first bytes of ws
@@ -155,15 +150,35 @@ int requant_all(sur_net *n)
     return PIC_OK;
 }
 
-// train: also clear the loss accumulators
-int forward(sur_net *n, const float *params, int B, bool train)
+// The training step's forward pass: every layer's output kept for the
+// backward pass; also clears the loss accumulators.
+int forward(sur_net *n, const float *params, int B)
 {
-    SUR_TRY(surx_features(params, n->feat, train ? n->loss : nullptr, n->X, B, n->stream));
+    SUR_TRY(surx_features(params, n->feat, n->loss, n->X, B, n->stream));
     for (int l = 0; l < SUR_LAYERS; ++l) {
         const __bf16 *in = l == 0 ? n->feat : n->yb[l - 1];
         __bf16 *yb = l < SUR_LAYERS - 1 ? n->yb[l] : nullptr;
         SUR_TRY(surx_conv_fwd(l, in, n->L[l].wf, n->L[l].bias, n->yf[l], yb, n->X, B, n->stream));
     }
+    return PIC_OK;
+}
+
+// Forward pass of any batch straight into the caller's output (surx_net's modes).
+int infer(sur_net *n, int mode, const float *params, const double *n0, int B, void *out)
+{
+    const __bf16 *wf[SUR_LAYERS];
+    const float *bias[SUR_LAYERS];
+    for (int l = 0; l < SUR_LAYERS; ++l) {
+        wf[l] = n->L[l].wf;
+        bias[l] = n->L[l].bias;
+    }
+    // pieces of at most 2^27 positions: the grid stays far below its limits
+    const int piece = (int)std::max<long long>(1, (1ll << 27) / n->X);
+    const size_t rows = mode == 1 ? 2 : SUR_OUT, size = mode == 0 ? sizeof(float) : sizeof(double);
+    for (int b0 = 0; b0 < B; b0 += piece)
+        SUR_TRY(surx_net(wf, bias, mode, params + (size_t)4 * b0, n0 ? n0 + b0 : nullptr,
+                         static_cast<char *>(out) + (size_t)b0 * rows * n->X * size, n->X, std::min(piece, B - b0),
+                         n->stream));
     return PIC_OK;
 }
 
@@ -205,48 +220,8 @@ int copy_out(sur_net *n, bool grads, float *w, float *b)
     return PIC_OK;
 }
 
-// ---------------------------------------------------------------------------
-// Scratch of the allocation-free forward pass (sur_forward_noalloc): one
-// file-scope device array, so that the call needs no device memory beyond
-// the handle's weights and the caller's inputs and outputs.  Every GPU the
-// library runs on holds its own copy until the process ends.  In host code
-// the array's name is not a device address: its address on a GPU comes from
-// hipGetSymbolAddress with that GPU current (scratch_on_current_device).
-// ---------------------------------------------------------------------------
-constexpr size_t SCRATCH_BYTES = (size_t)12 << 20;
-// per sample and cell: features (16 bf16), a hidden output in FP32 (64,
-// overwritten layer after layer), the last layer's FP32 output (48 padded
-// channels) and two bf16 ping-pong copies of the hidden activations (64 each)
-constexpr size_t SCRATCH_PER_POSITION = 16 * 2 + 64 * 4 + 48 * 4 + 2 * 64 * 2;
-
-}  // namespace
-
-static __device__ __align__(256) char scratch[SCRATCH_BYTES];
-
-namespace {
-
-constexpr int MAX_DEVICES = 64;
-std::mutex g_scratch_mu;
-char *g_scratch_ptr[MAX_DEVICES] = {};
-
-// The scratch array's address on the current GPU, looked up once per GPU.
-int scratch_on_current_device(int *device, char **ptr)
-{
-    int dev = -1;
-    SUR_TRY(hipGetDevice(&dev));
-    if (dev < 0 || dev >= MAX_DEVICES) return fail(PIC_EINVAL, "device index beyond the scratch table");
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (!g_scratch_ptr[dev]) {
-        void *p = nullptr;
-        hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p)
-            return fail(PIC_EHIP, std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e));
-        g_scratch_ptr[dev] = static_cast<char *>(p);
-    }
-    *device = dev;
-    *ptr = g_scratch_ptr[dev];
-    return PIC_OK;
-}
+// The most cells per sample that sur_forward_noalloc takes.
+constexpr int NOALLOC_MAX_CELLS = 17096;
 
 }  // namespace
 
@@ -284,8 +259,7 @@ int sur_create(int max_batch, int cells, void *dev_workspace, size_t bytes, void
     Bump bp{n->ws};
     layout(*n, bp);
     auto cleanup = [&](int code) { delete n; return code; };
-    // the allocation-free forward's scratch on this GPU (set-up, once per GPU)
-    if ((rc = scratch_on_current_device(&n->device, &n->scratch))) return cleanup(rc);
+    if (hipGetDevice(&n->device) != hipSuccess) return cleanup(fail(PIC_EHIP, "hipGetDevice failed"));
     if (hipMemsetAsync(n->ws, 0, n->param_bytes, n->stream) != hipSuccess)
         return cleanup(fail(PIC_EHIP, "hipMemsetAsync failed"));
     for (int l = 0; l < SUR_LAYERS; ++l) {
@@ -331,43 +305,20 @@ int sur_forward(sur_net *n, const float *dev_params, int batch, float *dev_out)
 {
     if (!n || !dev_params || !dev_out) return fail(PIC_EINVAL, "bad arguments");
     if (batch < 1 || batch > n->bmax) return fail(PIC_EINVAL, "batch exceeds the workspace's max_batch");
-    int rc = forward(n, dev_params, batch, false);
-    if (rc) return rc;
-    SUR_TRY(surx_unpack(n->yf[SUR_LAYERS - 1], dev_out, n->X, batch, n->stream));
-    return PIC_OK;
+    return infer(n, 0, dev_params, nullptr, batch, dev_out);
 }
 
 int sur_forward_noalloc(sur_net *n, const float *dev_params, int batch, float *dev_out)
 {
     if (!n || !dev_params || !dev_out) return fail(PIC_EINVAL, "bad arguments");
     if (batch < 1) return fail(PIC_EINVAL, "batch must be positive");
-    const size_t per_sample = SCRATCH_PER_POSITION * (size_t)n->X;
-    const int chunk = (int)std::min<size_t>(SCRATCH_BYTES / per_sample, (size_t)batch);
-    if (chunk < 1)
-        return fail(PIC_EINVAL, "cells beyond the scratch array: at most " +
-                                    std::to_string(SCRATCH_BYTES / SCRATCH_PER_POSITION) + " per sample");
+    if (n->X > NOALLOC_MAX_CELLS)
+        return fail(PIC_EINVAL, "cells beyond the allocation-free path's scratch limit: at most " +
+                                    std::to_string(NOALLOC_MAX_CELLS) + " per sample");
     int dev = -1;
     SUR_TRY(hipGetDevice(&dev));
     if (dev != n->device) return fail(PIC_EINVAL, "the handle's GPU is not the current device");
-    char *base = n->scratch;     // the array's address on this GPU, never its host-side name
-    const size_t P = (size_t)chunk * n->X;
-    __bf16 *feat = reinterpret_cast<__bf16 *>(base);
-    float *yf = reinterpret_cast<float *>(base + P * 16 * 2);
-    float *yout = reinterpret_cast<float *>(base + P * (16 * 2 + 64 * 4));
-    __bf16 *yb[2] = {reinterpret_cast<__bf16 *>(base + P * (16 * 2 + 64 * 4 + 48 * 4)),
-                     reinterpret_cast<__bf16 *>(base + P * (16 * 2 + 64 * 4 + 48 * 4 + 64 * 2))};
-    for (int b0 = 0; b0 < batch; b0 += chunk) {
-        const int nb = std::min(chunk, batch - b0);
-        SUR_TRY(surx_features(dev_params + (size_t)4 * b0, feat, nullptr, n->X, nb, n->stream));
-        for (int l = 0; l < SUR_LAYERS; ++l) {
-            const __bf16 *in = l == 0 ? feat : yb[(l - 1) & 1];
-            const bool last = l == SUR_LAYERS - 1;
-            SUR_TRY(surx_conv_fwd(l, in, n->L[l].wf, n->L[l].bias, last ? yout : yf, last ? nullptr : yb[l & 1], n->X,
-                                  nb, n->stream));
-        }
-        SUR_TRY(surx_unpack(yout, dev_out + (size_t)b0 * SUR_OUT * n->X, n->X, nb, n->stream));
-    }
-    return PIC_OK;
+    return infer(n, 0, dev_params, nullptr, batch, dev_out);
 }
 
 int sur_train_step(sur_net *n, const float *dev_params, const float *dev_target, int batch, float lr, double *loss)
@@ -377,7 +328,7 @@ int sur_train_step(sur_net *n, const float *dev_params, const float *dev_target,
     if (!(lr > 0.0f)) return fail(PIC_EINVAL, "learning rate must be positive");
     const int X = n->X;
     // the forward pass zeroes the loss accumulators (features kernel)
-    int rc = forward(n, dev_params, batch, true);
+    int rc = forward(n, dev_params, batch);
     if (rc) return rc;
     SUR_TRY(surx_loss(n->yf[SUR_LAYERS - 1], dev_target, n->dz[0], n->loss, X, batch, n->stream));
     n->t += 1;
@@ -417,20 +368,14 @@ int sur_densities(sur_net *n, const float *dev_params, const double *dev_n0, int
 {
     if (!n || !dev_params || !dev_n0 || !dev_dens) return fail(PIC_EINVAL, "bad arguments");
     if (batch < 1 || batch > n->bmax) return fail(PIC_EINVAL, "batch exceeds the workspace's max_batch");
-    int rc = forward(n, dev_params, batch, false);
-    if (rc) return rc;
-    SUR_TRY(surx_to_densities(n->yf[SUR_LAYERS - 1], dev_n0, dev_dens, n->X, batch, n->stream));
-    return PIC_OK;
+    return infer(n, 1, dev_params, dev_n0, batch, dev_dens);
 }
 
 int sur_state(sur_net *n, const float *dev_params, const double *dev_n0, int batch, double *dev_state)
 {
     if (!n || !dev_params || !dev_n0 || !dev_state) return fail(PIC_EINVAL, "bad arguments");
     if (batch < 1 || batch > n->bmax) return fail(PIC_EINVAL, "batch exceeds the workspace's max_batch");
-    int rc = forward(n, dev_params, batch, false);
-    if (rc) return rc;
-    SUR_TRY(surx_to_state(n->yf[SUR_LAYERS - 1], dev_params, dev_n0, dev_state, n->X, batch, n->stream));
-    return PIC_OK;
+    return infer(n, 2, dev_params, dev_n0, batch, dev_state);
 }
 
 const char *sur_last_error(void) { return g_err.c_str(); }

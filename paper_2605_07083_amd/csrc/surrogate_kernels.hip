@@ -3,7 +3,7 @@
 // (phi / V, ln(n_e / n0), ln(n_i / n0)) at the X cell centres of a diode.
 //
 // Net: 6 conv1d layers, kernel 5, zero padding 2, channels
-// 16 -> 64 -> 64 -> 64 -> 64 -> 64 -> 3 (stored padded to 16), tanh after
+// 16 -> 64 -> 64 -> 64 -> 64 -> 64 -> 39 (stored padded to 48), tanh after
 // layers 1-5.  Input channels: the 4 normalised parameters and 12 functions of
 // the position.  Weights are BF16 (FP32 master copies for Adam), activations
 // enter every layer as BF16, all products accumulate in FP32 on
@@ -12,7 +12,7 @@
 // Layouts: activations and gradients channels last, act[b][x][c]: the forward
 // and input-gradient GEMMs read them along K (channels) with 16-byte reads, the
 // weight gradient (K = positions) reads the same tiles transposed with
-// ds_read_b64_tr_b16; forward weights Wf[co][t*Cin + ci] (K contiguous),
+// ds_read_b64_tr_b16; forward weights Wf in fragment order (see frag_at),
 // transposed weights for the input gradient Wb[ci][t*Cout + co]; both padded
 // with zeros to a multiple of 32 in K.
 //
@@ -20,10 +20,13 @@
 // B[8(l/16)+i][l%16], i = 0..7, and receives D[4(l/16)+i][l%16], i = 0..3.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace sur {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int KS = 5;     // kernel size
@@ -55,11 +58,55 @@ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, u
     return make_uint4(c0, c1, c2, c3);
 }
 
+// Place of forward weight (co, kappa = t*CIN + ci) in fragment order: the
+// layer's weights as matrix-core fragments of 16 output channels x 32 kappa,
+// output tile by output tile, each fragment's 64 lanes x 8 elements in a row.
+// A wave reads a fragment as one contiguous kilobyte.
+__device__ __forceinline__ int frag_at(int co, int kappa, int kp)
+{
+    return (((co >> 4) * (kp >> 5) + (kappa >> 5)) * 64 + ((kappa & 31) >> 3) * 16 + (co & 15)) * 8 + (kappa & 7);
+}
+
 // ---------------------------------------------------------------------------
 // Input features.  params[b] = (Gamma m^-2 s^-1, T_c K, V volts, n_g m^-3) are
 // mapped to [-1, 1] over the training ranges (log scale for the flux and the
 // density); the position features resolve both sheaths and the interior.
 // ---------------------------------------------------------------------------
+// The features of position x in four parts of similar cost (PART 0..3: f0..f3,
+// f6..f9, f10..f11, the rest), each written to its place of f.
+template <int PART>
+__device__ __forceinline__ void features_part(const float *__restrict__ p, int x, int X, __bf16 *f)
+{
+    const float u = ((float)x + 0.5f) / (float)X;
+    if constexpr (PART == 0) {
+        const float g = p[0], T = p[1], V = p[2], ng = p[3];
+        f[0] = (__bf16)(2.0f * (log10f(g / 1e19f) / log10f(12.0f)) - 1.0f);
+        f[1] = (__bf16)((T - 2000.0f) / 200.0f);
+        f[2] = (__bf16)((V - 12.5f) / 7.5f);
+        f[3] = (__bf16)(2.0f * log10f(ng / 1e21f) - 1.0f);
+    } else if constexpr (PART == 1) {
+        float s1, c1, s2, c2;
+        sincospif(u, &s1, &c1);
+        sincospif(2.0f * u, &s2, &c2);
+        f[6] = (__bf16)s1;
+        f[7] = (__bf16)c1;
+        f[8] = (__bf16)s2;
+        f[9] = (__bf16)c2;
+    } else if constexpr (PART == 2) {
+        float s4, c4;
+        sincospif(4.0f * u, &s4, &c4);
+        f[10] = (__bf16)s4;
+        f[11] = (__bf16)c4;
+    } else {
+        f[4] = (__bf16)(2.0f * u - 1.0f);
+        f[5] = (__bf16)(1.0f - 2.0f * u);
+        f[12] = (__bf16)__expf(-64.0f * u);
+        f[13] = (__bf16)__expf(-64.0f * (1.0f - u));
+        f[14] = (__bf16)__expf(-16.0f * u);
+        f[15] = (__bf16)__expf(-16.0f * (1.0f - u));
+    }
+}
+
 __global__ void k_features(const float *__restrict__ params, __bf16 *__restrict__ feat, double *__restrict__ loss0,
                            int X, int B)
 {
@@ -67,27 +114,14 @@ __global__ void k_features(const float *__restrict__ params, __bf16 *__restrict_
     if (idx < LOSS_SLOTS && loss0) loss0[idx] = 0.0;     // the training step's loss accumulators
     if (idx >= X * B) return;
     const int b = idx / X, x = idx - b * X;
-    const float g = params[4 * b + 0], T = params[4 * b + 1], V = params[4 * b + 2], ng = params[4 * b + 3];
-    const float u = ((float)x + 0.5f) / (float)X;
-    float f[16];
-    f[0] = 2.0f * (log10f(g / 1e19f) / log10f(12.0f)) - 1.0f;
-    f[1] = (T - 2000.0f) / 200.0f;
-    f[2] = (V - 12.5f) / 7.5f;
-    f[3] = 2.0f * log10f(ng / 1e21f) - 1.0f;
-    f[4] = 2.0f * u - 1.0f;
-    f[5] = 1.0f - 2.0f * u;
-    float s1, c1, s2, c2, s4, c4;
-    sincospif(u, &s1, &c1);
-    sincospif(2.0f * u, &s2, &c2);
-    sincospif(4.0f * u, &s4, &c4);
-    f[6] = s1; f[7] = c1; f[8] = s2; f[9] = c2; f[10] = s4; f[11] = c4;
-    f[12] = __expf(-64.0f * u);
-    f[13] = __expf(-64.0f * (1.0f - u));
-    f[14] = __expf(-16.0f * u);
-    f[15] = __expf(-16.0f * (1.0f - u));
+    __bf16 f[16];
+    features_part<0>(params + 4 * b, x, X, f);
+    features_part<1>(params + 4 * b, x, X, f);
+    features_part<2>(params + 4 * b, x, X, f);
+    features_part<3>(params + 4 * b, x, X, f);
     __bf16 *o = feat + (size_t)idx * 16;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) o[c] = (__bf16)f[c];
+    for (int c = 0; c < 16; ++c) o[c] = f[c];
 }
 
 // ---------------------------------------------------------------------------
@@ -113,6 +147,24 @@ __device__ __forceinline__ void stage_rows(__bf16 *lds, const __bf16 *__restrict
     for (int k = 0; k < N; ++k) {
         const int v = threadIdx.x + k * THREADS;
         if (v < ROWS * V) *reinterpret_cast<bf16x8 *>(lds + (v / V) * (KP + 8) + (v % V) * 8) = r[k];
+    }
+}
+
+// A layer's forward weights, already in fragment order, copied as they are.
+template <int N, int THREADS>
+__device__ __forceinline__ void stage_frags(__bf16 *lds, const __bf16 *__restrict__ src)
+{
+    constexpr int PER = (N / 8 + THREADS - 1) / THREADS;
+    bf16x8 r[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int v = threadIdx.x + k * THREADS;
+        r[k] = v < N / 8 ? load8(src + v * 8) : zero8();
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int v = threadIdx.x + k * THREADS;
+        if (v < N / 8) *reinterpret_cast<bf16x8 *>(lds + v * 8) = r[k];
     }
 }
 
@@ -149,7 +201,7 @@ __global__ __launch_bounds__(CONV_THREADS) void k_conv_fwd(const __bf16 *__restr
     constexpr int NI = (FW_ROWS * IV + CONV_THREADS - 1) / CONV_THREADS;
     constexpr int OS = COUT + 4;                                 // staged output row (floats)
     static_assert(CIN == 16 || CIN == 64, "input row stride");
-    __shared__ __bf16 wl[COUT * (KP + 8)];
+    __shared__ __align__(16) __bf16 wl[COUT * KP];
     __shared__ __align__(16) __bf16 it[FW_ROWS * SIN];
     __shared__ __align__(16) float ot[CONV_THREADS / 64][16 * OS];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -165,7 +217,7 @@ __global__ __launch_bounds__(CONV_THREADS) void k_conv_fwd(const __bf16 *__restr
             const int v = threadIdx.x + k * CONV_THREADS, x = xb - PAD + v / IV;
             r[k] = v < FW_ROWS * IV && x >= 0 && x < X ? load8(inb + (size_t)x * CIN + (v % IV) * 8) : zero8();
         }
-        stage_rows<COUT, KP, CONV_THREADS>(wl, Wf);
+        stage_frags<COUT * KP, CONV_THREADS>(wl, Wf);
 #pragma unroll
         for (int k = 0; k < NI; ++k) {
             const int v = threadIdx.x + k * CONV_THREADS;
@@ -190,7 +242,7 @@ __global__ __launch_bounds__(CONV_THREADS) void k_conv_fwd(const __bf16 *__restr
             }
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const bf16x8 bw = *reinterpret_cast<const bf16x8 *>(wl + (nt * 16 + m) * (KP + 8) + kappa);
+                const bf16x8 bw = load8(wl + ((nt * (KP / 32) + ks) * 64 + lane) * 8);
                 acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw, acc[nt], 0, 0, 0);
             }
         }
@@ -460,7 +512,6 @@ __global__ __launch_bounds__(BW_THREADS) void k_conv_bwd(const __bf16 *__restric
             const int v = tid + k * BW_THREADS;
             if (v >= BW_ROWS * S::IV) continue;
             if constexpr (DG) {
-                typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
                 bf16x4 h;
                 h[0] = (__bf16)ry[k].x;
                 h[1] = (__bf16)ry[k].y;
@@ -640,8 +691,8 @@ __global__ __launch_bounds__(BW_THREADS) void k_conv_bwd(const __bf16 *__restric
 }
 
 // The gradient of one layer from its partials, then Adam on the FP32 master
-// weights and biases and the BF16 copies of the weights: forward layout
-// Wf[co][kappa] and transposed Wb[ci][t*COUTP + co].  A block takes 64
+// weights and biases and the BF16 copies of the weights: forward Wf in
+// fragment order and transposed Wb[ci][t*COUTP + co].  A block takes 64
 // consecutive entries of the padded weights [COUTP][KP] followed by the
 // biases; wave w sums the partials w, w + 16, ... of each, and the first
 // wave adds the 16 sums in wave order and updates.
@@ -694,7 +745,7 @@ __global__ __launch_bounds__(RA_WAVES * 64) void k_reduce_adam(
     *wp = nwv;
     if (isw) {
         const __bf16 v = (__bf16)(live ? nwv : 0.0f);
-        Wf[i] = v;
+        Wf[frag_at(co, kappa, kp)] = v;
         if (kappa < KS * cin) {
             const int t = kappa / cin, ci = kappa - t * cin;
             Wb[(size_t)ci * kpb + t * coutp + co] = v;
@@ -702,7 +753,7 @@ __global__ __launch_bounds__(RA_WAVES * 64) void k_reduce_adam(
     }
 }
 
-// masters [COUTP][KP] (kappa = t*CIN + ci) -> Wf (same layout, bf16) and
+// masters [COUTP][KP] (kappa = t*CIN + ci) -> Wf (fragment order, bf16) and
 // Wb[ci][t*COUTP + co] (padded to KPB)
 __global__ void k_requant(const float *__restrict__ wm, __bf16 *__restrict__ Wf, __bf16 *__restrict__ Wb, int cin,
                           int coutp, int cout_real, int kp, int kpb)
@@ -712,7 +763,7 @@ __global__ void k_requant(const float *__restrict__ wm, __bf16 *__restrict__ Wf,
     const int co = i / kp, kappa = i - co * kp;
     const bool live = co < cout_real && kappa < KS * cin;
     const __bf16 v = (__bf16)(live ? wm[i] : 0.0f);
-    Wf[i] = v;
+    Wf[frag_at(co, kappa, kp)] = v;
     if (kappa < KS * cin) {
         const int t = kappa / cin, ci = kappa - t * cin;
         Wb[(size_t)ci * kpb + t * coutp + co] = v;
@@ -738,45 +789,342 @@ __global__ void k_init_weights(float *__restrict__ wm, int cin, int coutp, int c
     wm[i] = v;
 }
 
-// Network output -> densities per cell for the warm-start loader:
-// dens[d][0][x] = n0 exp(out[d][x][1]), dens[d][1][x] = n0 exp(out[d][x][2]).
-__global__ void k_to_densities(const float *__restrict__ out, const double *__restrict__ n0, double *__restrict__ dens,
-                               int X, int B)
+// ---------------------------------------------------------------------------
+// The whole forward pass in one kernel: features, the six convolutions and
+// the conversion to the caller's output.
+//
+// A block of four waves takes T output positions of one sample.  A layer
+// needs two positions more on each side than the next, so the block works on
+// T + 20 <= `rows` rows, and each layer's valid rows shrink by two at both
+// ends: the hidden activations never leave the block.  They live in LDS
+// as bfloat16 rows of 64 channels (two buffers, a layer reads one and writes
+// the other), the 16-byte groups of a row permuted by the row's low bits so
+// that the 16 rows of a fragment read fall on different banks.
+//
+// Row r of a hidden layer is position x0 - 10 + r, stored at buffer row
+// r + 2; rows outside the sample are stored as zeros (the padding of the next
+// layer).  A layer is the GEMM  channels x positions, K = 5 CIN: a wave holds
+// C tiles of 16 output channels, their weights for the whole K in registers
+// (fragments read straight from global memory, the next layer's requested as
+// soon as this layer's products are done), and walks its share of the rows,
+// PB tiles of 16 positions at a time.
+// The product is taken as weights x activations, so that a lane receives four
+// consecutive channels of one position and stores them as one 8-byte LDS
+// write; the last layer is taken the other way round, so that a lane has four
+// consecutive positions of one channel, the caller's [channel][position]
+// order.
+//
+// Bound by the vector unit (the tanh of 64 samples takes 2/3 of the cycles, the
+// matrix cores 1/3), on one sample by the chain of layers.  One kernel per
+// layer was bound by its launches and by every activation written and read
+// again in FP32 and bfloat16.  Measured (2048 cells, the whole call, before and
+// after): 1 sample 53 -> 7.9 us, 8 samples 58 -> 14.3, 64 samples 131 -> 43 us
+// (610 TFLOP/s).
+// ---------------------------------------------------------------------------
+struct NetParams {
+    const __bf16 *w[6];      // forward weights, fragment order
+    const float *bias[6];
+};
+
+// bf16(tanhf(x)) of four values.  tanh x = 1 - 2 / (1 + e^2x) from the
+// hardware's exp2 and reciprocal is off by a few 1e-7 in absolute terms; the
+// two ends of that error interval almost always round to the same bfloat16,
+// which then is the one tanhf's result rounds to (checked for every float x;
+// half the absolute part of this margin still held).  Where they differ, for
+// one value in some thousands, tanhf itself decides.  About 13 instructions'
+// time per value instead of tanhf's 35.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= X * B) return;
-    const int b = idx / X, x = idx - b * X;
-    dens[((size_t)b * 2 + 0) * X + x] = n0[b] * exp((double)out[(size_t)idx * OUTP + 1]);
-    dens[((size_t)b * 2 + 1) * X + x] = n0[b] * exp((double)out[(size_t)idx * OUTP + 2]);
+    const bf16x2 r = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, r);
 }
 
-// Network output -> the state the warm-start loader reads, [b][OUT][x]:
-// densities as k_to_densities, phi = V out[0], the electron quantiles
-// (channels 3..20) times the 1 eV electron speed sqrt(e / m_e), the ion ones
-// (21..38) times the 1 eV ion speed sqrt(e / m_i).  params[b][2] is V.
-__global__ void k_to_state(const float *__restrict__ out, const float *__restrict__ params,
-                           const double *__restrict__ n0, double *__restrict__ state, int X, int B)
+// The value, and what is open: nonzero bits of `open` where the ends differ.
+__device__ __forceinline__ uint2 tanh4(f32x4 x, uint2 &open)
 {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= X * B) return;
-    const int b = idx / X, x = idx - b * X;
-    const float *o = out + (size_t)idx * OUTP;
-    double *st = state + (size_t)b * OUT * X + x;
-    const double ve = sqrt(1.602176634e-19 / 9.1093837015e-31);
-    const double vi = sqrt(1.602176634e-19 / (6.6464731e-27 - 9.1093837015e-31));
-    st[0] = n0[b] * exp((double)o[1]);
-    st[(size_t)X] = n0[b] * exp((double)o[2]);
-    st[(size_t)2 * X] = (double)params[(size_t)b * 4 + 2] * (double)o[0];
-    for (int c = 3; c < OUT; ++c) st[(size_t)c * X] = (double)o[c] * (c < 21 ? ve : vi);
+    constexpr float MARGIN = 1.2e-7f;
+    float lo[4], hi[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float t = __builtin_amdgcn_exp2f(x[i] * 2.8853900817779268f);   // 2 / ln 2
+        const float r = __builtin_amdgcn_rcpf(t + 1.0f);
+        lo[i] = __builtin_fmaf(-2.0f * (1.0f + MARGIN), r, 1.0f - MARGIN);
+        hi[i] = __builtin_fmaf(-2.0f * (1.0f - MARGIN), r, 1.0f + MARGIN);
+    }
+    const uint2 a = make_uint2(pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]));
+    open = make_uint2(a.x ^ pack_bf16(hi[0], hi[1]), a.y ^ pack_bf16(hi[2], hi[3]));
+    return a;
 }
 
-// Network output [b][x][OUTP] -> caller layout [b][OUT][x].
-__global__ void k_unpack(const float *__restrict__ y, float *__restrict__ out, int X, int B)
+// tanhf where it is open in some lane (a lane whose ends agree gets the same
+// bits from it).
+__device__ __forceinline__ void tanh4_settle(f32x4 x, uint2 open, uint2 &h)
 {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= X * B) return;
-    const int b = idx / X, x = idx - b * X;
-    for (int c = 0; c < OUT; ++c) out[((size_t)b * OUT + c) * X + x] = y[(size_t)idx * OUTP + c];
+    if (__any(open.x)) h.x = pack_bf16(tanhf(x[0]), tanhf(x[1]));
+    if (__any(open.y)) h.y = pack_bf16(tanhf(x[2]), tanhf(x[3]));
+}
+
+// the caller's arrays need no more than their elements' alignment
+typedef float out_f32x4 __attribute__((__vector_size__(16), aligned(4)));
+typedef double out_f64x2 __attribute__((__vector_size__(16), aligned(8)));
+
+enum NetOut { NET_OUT, NET_DENSITIES, NET_STATE };
+
+constexpr int NET_THREADS = 256;
+constexpr int NET_HALO = 20;     // rows beyond the block's outputs, both sides together
+
+// rows: a multiple of 16 C PB; grid (tiles x samples); LDS 2 (rows + 4) x 64
+// bfloat16 and 6 x 64 biases.
+template <int C, int MODE>
+__global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const float *__restrict__ params,
+                                                        const double *__restrict__ n0, void *__restrict__ outp, int X,
+                                                        int tiles, int T, int rows)
+{
+    extern __shared__ __align__(16) __bf16 net_lds[];
+    constexpr int FS = 24;                         // feature row stride (48 bytes)
+    constexpr int PB = 2;                          // position tiles in flight
+    constexpr int DEP = 2;                         // fragments in flight per position tile
+    const int brows = rows + 4;                    // buffer rows: two spare ones at each end
+    const int G = rows / (16 * C * PB);            // groups of PB position tiles per wave
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = lane & 15, kb = lane >> 4;
+    const int cg = w % (4 / C), rw = w / (4 / C) * (G * PB * 16);  // this wave's channel tiles and first row
+    const int b = blockIdx.x / tiles;
+    const int x0 = (blockIdx.x - b * tiles) * T;
+    const float *pb = params + (size_t)b * 4;
+
+    bf16x8 W[C][10];                               // a layer's weights
+    // unconditional (a wave without a tile in the last layer reads the last
+    // one's): a load on one path of a branch would make the compiler wait for
+    // every load in flight where the paths meet
+    auto load_weights = [&](int l, auto nks) {
+        constexpr int NKS = decltype(nks)::value;
+        const __bf16 *wf = np.w[l];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int nt = min(cg * C + c, l == 5 ? OUTP / 16 - 1 : 3);
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) W[c][ks] = load8(wf + (nt * NKS + ks) * 512 + (unsigned)(lane * 8));
+        }
+    };
+    using K3 = std::integral_constant<int, 3>;
+    using K10 = std::integral_constant<int, 10>;
+    load_weights(0, K3{});
+    // every layer's biases in LDS: read there, they wait for no weights
+    float *bias_lds = reinterpret_cast<float *>(net_lds + 2 * brows * 64);
+    for (int i = threadIdx.x; i < 6 * 64; i += NET_THREADS) bias_lds[i] = i < 5 * 64 + OUTP ? np.bias[i >> 6][i & 63] : 0.0f;
+    // the features of positions x0 - 12 .. (zero outside the sample), a part per wave
+    __bf16 *F = net_lds + brows * 64;
+    auto put_features = [&](auto part) {
+        constexpr int PART = decltype(part)::value;
+        for (int q = lane; q < brows; q += 64) {
+            const int x = x0 - 12 + q;
+            __bf16 f[16] = {};
+            if (x >= 0 && x < X) features_part<PART>(pb, x, X, f);
+            uint32_t *o = reinterpret_cast<uint32_t *>(F + q * FS);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int of = c < 2 ? 0 : c == 2 ? 3 : c < 5 ? 1 : c == 5 ? 2 : 3;
+                if (of == PART) {
+                    const bf16x2 v = {f[2 * c], f[2 * c + 1]};
+                    o[c] = __builtin_bit_cast(uint32_t, v);
+                }
+            }
+        }
+    };
+    switch (w) {
+    case 0: put_features(std::integral_constant<int, 0>{}); break;
+    case 1: put_features(std::integral_constant<int, 1>{}); break;
+    case 2: put_features(std::integral_constant<int, 2>{}); break;
+    default: put_features(std::integral_constant<int, 3>{}); break;
+    }
+    // element offset of the lane's 16-byte group of fragment ks in the rows from `first` on
+    auto group = [&](int first, int ks) {
+        const int q = first + m + (ks >> 1), g = (ks & 1) * 4 + kb;
+        return q * 64 + ((g ^ (q & 7)) << 3);
+    };
+    int off[10];
+#pragma unroll
+    for (int ks = 0; ks < 10; ++ks) off[ks] = group(0, ks);
+    __syncthreads();
+
+    f32x4 bias[C];
+    auto load_bias = [&](int l) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            bias[c] = *reinterpret_cast<const f32x4 *>(bias_lds + l * 64 + (cg * C + c) * 16 + kb * 4);
+    };
+    // bias, tanh, bfloat16, into rows r + 2 of dst; zero outside the sample
+    const bool inside = x0 >= 10 && x0 - 10 + rows <= X;      // the block's rows all lie in the sample
+    int put[C];                                    // the lane's element offset in row m + 2
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int q = m + 2, g = (cg * C + c) * 2 + (kb >> 1);
+        put[c] = q * 64 + ((g ^ (q & 7)) << 3) + (kb & 1) * 4;
+    }
+    auto activation = [&](__bf16 *dst, const f32x4 (&acc)[C][PB], int r0) {
+        __bf16 *row = dst + r0 * 64;
+#pragma unroll
+        for (int p = 0; p < PB; ++p) {
+            uint2 h[C], open[C];
+            uint32_t any = 0;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                h[c] = tanh4(acc[c][p] + bias[c], open[c]);
+                any |= open[c].x | open[c].y;
+            }
+            if (__builtin_expect(__any(any), 0)) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) tanh4_settle(acc[c][p] + bias[c], open[c], h[c]);
+            }
+            const int x = x0 - 10 + r0 + p * 16 + m;
+            if (!inside && (x < 0 || x >= X)) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) h[c] = make_uint2(0u, 0u);
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) *reinterpret_cast<uint2 *>(row + p * 1024 + put[c]) = h[c];
+        }
+    };
+    // the wave's groups that any output depends on
+    const int groups = min(G, max(0, (T + NET_HALO - rw + PB * 16 - 1) / (PB * 16)));
+
+    f32x4 acc[C][PB];
+    auto first_products = [&](int r0) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int p = 0; p < PB; ++p) acc[c][p] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 3; ++ks) {
+            const int kappa = ks * 32 + kb * 8;
+#pragma unroll
+            for (int p = 0; p < PB; ++p) {
+                // row r reads the features of positions x - 2 .. x + 2: rows r .. r + 4
+                const bf16x8 a = kappa < 80 ? load8(F + (r0 + p * 16 + m + (kappa >> 4)) * FS + (kappa & 15)) : zero8();
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[c][ks], a, acc[c][p], 0, 0, 0);
+            }
+        }
+    };
+    // K = 5 x 64 over the rows of src from r0 on: DEP fragments per position
+    // tile in flight ahead of the matrix cores
+    auto products = [&](const __bf16 *src, int r0) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int p = 0; p < PB; ++p) acc[c][p] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        bf16x8 a[DEP][PB];
+        const __bf16 *row = src + r0 * 64;
+#pragma unroll
+        for (int ks = 0; ks < DEP; ++ks)
+#pragma unroll
+            for (int p = 0; p < PB; ++p) a[ks][p] = load8(row + p * 1024 + off[ks]);
+        __builtin_amdgcn_sched_group_barrier(0x100, DEP * PB, 0);
+#pragma unroll
+        for (int ks = 0; ks < 10; ++ks) {
+#pragma unroll
+            for (int p = 0; p < PB; ++p)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[c][ks], a[ks % DEP][p], acc[c][p], 0, 0, 0);
+            __builtin_amdgcn_sched_group_barrier(0x8, C * PB, 0);
+            if (ks + DEP < 10) {
+#pragma unroll
+                for (int p = 0; p < PB; ++p) a[ks % DEP][p] = load8(row + p * 1024 + off[ks + DEP]);
+                __builtin_amdgcn_sched_group_barrier(0x100, PB, 0);
+            }
+        }
+    };
+
+    load_bias(0);
+#pragma unroll 1
+    for (int g = 0; g < groups - 1; ++g) {
+        first_products(rw + g * PB * 16);
+        activation(net_lds, acc, rw + g * PB * 16);
+    }
+    const int last = rw + max(groups - 1, 0) * PB * 16;      // the wave's last group
+    first_products(last);
+    load_weights(1, K10{});
+    activation(net_lds, acc, last);
+    __syncthreads();
+#pragma unroll 1
+    for (int l = 1; l < 5; ++l) {
+        const __bf16 *src = net_lds + ((l - 1) & 1) * brows * 64;
+        __bf16 *dst = net_lds + (l & 1) * brows * 64;
+        load_bias(l);
+#pragma unroll 1
+        for (int g = 0; g < groups - 1; ++g) {
+            products(src, rw + g * PB * 16);
+            activation(dst, acc, rw + g * PB * 16);
+        }
+        products(src, last);
+        load_weights(l + 1, K10{});      // their registers are free: the next layer's, beside the activation
+        activation(dst, acc, last);
+        __syncthreads();
+    }
+    // the last layer: row s is output position x0 + s, its inputs rows s + 10 .. s + 14
+#pragma unroll
+    for (int ks = 0; ks < 10; ++ks) off[ks] = group(10, ks);
+#pragma unroll 1
+    for (int g = 0; g < G; ++g) {
+        const int s0 = rw + g * PB * 16;
+        if (s0 >= T) break;
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int p = 0; p < PB; ++p) acc[c][p] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 10; ++ks) {
+#pragma unroll
+            for (int p = 0; p < PB; ++p) {
+                if (s0 + p * 16 >= T) continue;      // the buffer's rows end at T + 24
+                const bf16x8 a = load8(net_lds + (s0 + p * 16) * 64 + off[ks]);
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    if (cg * C + c < OUTP / 16)
+                        acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, W[c][ks], acc[c][p], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < PB; ++p) {
+            const int s = s0 + p * 16 + kb * 4, x = x0 + s;     // four positions (T and X are multiples of 4)
+            if (s >= T || x >= X) continue;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const int co = (cg * C + c) * 16 + m;
+                if (co >= OUT) continue;
+                const float bc = bias_lds[5 * 64 + co];
+                const f32x4 v = acc[c][p] + (f32x4){bc, bc, bc, bc};
+                if constexpr (MODE == NET_OUT) {
+                    *reinterpret_cast<out_f32x4 *>(static_cast<float *>(outp) + ((size_t)b * OUT + co) * X + x) = v;
+                } else {
+                    // densities n0 exp(out[1]), n0 exp(out[2]); phi = V out[0]; the electron quantiles
+                    // (channels 3..20) times the 1 eV electron speed sqrt(e / m_e), the ion ones (21..38)
+                    // times the 1 eV ion speed sqrt(e / m_i)
+                    if (MODE == NET_DENSITIES && co != 1 && co != 2) continue;
+                    double d[4] = {v[0], v[1], v[2], v[3]};
+                    if (co == 1 || co == 2) {
+                        const double n = n0[b];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) d[i] = n * exp(d[i]);
+                    } else {
+                        const double ve = sqrt(1.602176634e-19 / 9.1093837015e-31);
+                        const double vi = sqrt(1.602176634e-19 / (6.6464731e-27 - 9.1093837015e-31));
+                        const double f = co == 0 ? (double)pb[2] : co < 21 ? ve : vi;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) d[i] *= f;
+                    }
+                    const int row = co == 0 ? 2 : co < 3 ? co - 1 : co, rows = MODE == NET_STATE ? OUT : 2;
+                    out_f64x2 *o = reinterpret_cast<out_f64x2 *>(static_cast<double *>(outp) +
+                                                                 ((size_t)b * rows + row) * X + x);
+                    o[0] = (out_f64x2){d[0], d[1]};
+                    o[1] = (out_f64x2){d[2], d[3]};
+                }
+            }
+        }
+    }
 }
 
 }  // namespace sur
@@ -860,21 +1208,56 @@ extern "C" hipError_t surx_init_weights(float *wm, int cin, int coutp, int cout_
     return hipGetLastError();
 }
 
-extern "C" hipError_t surx_to_densities(const float *out, const double *n0, double *dens, int X, int B, hipStream_t s)
+constexpr int NET_CUS = 256;
+
+template <int C>
+static hipError_t launch_net(const NetParams &np, int mode, const float *params, const double *n0, void *out, int X,
+                             int B, int rows, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_to_densities, dim3((X * B + 255) / 256), dim3(256), 0, s, out, n0, dens, X, B);
+    const int most = rows - NET_HALO;
+    // equal tiles, a multiple of 4 positions each
+    const int tiles = (X + most - 1) / most, T = ((X + tiles - 1) / tiles + 3) / 4 * 4;
+    const dim3 g((unsigned)tiles * (unsigned)B), t(NET_THREADS);
+    const size_t lds = (size_t)2 * (rows + 4) * 64 * sizeof(__bf16) + 6 * 64 * sizeof(float);
+    auto *kernel = mode == NET_OUT ? k_net<C, NET_OUT> : mode == NET_DENSITIES ? k_net<C, NET_DENSITIES>
+                                                                              : k_net<C, NET_STATE>;
+    hipLaunchKernelGGL(kernel, g, t, lds, s, np, params, n0, out, X, tiles, T, rows);
     return hipGetLastError();
 }
 
-extern "C" hipError_t surx_to_state(const float *out, const float *params, const double *n0, double *state, int X,
-                                    int B, hipStream_t s)
+// Forward pass of B samples into the caller's output: mode 0 the network's
+// channels [b][39][x] (float), 1 densities [b][2][x], 2 the loader's state
+// [b][39][x] (double; n0 per sample).
+//
+// Rows per block: few rows give many short blocks, but 20 of them are halo
+// computed again by the neighbours.  A call takes about the longer of a
+// block's chain of layers, 4.5 us + 0.105 us a row, and the work of the most
+// loaded CU, 5 us + 0.064 us x (rows + 8) x its blocks; the rows with the
+// least of it are taken.  Measured (2048 cells; 32 / 64 / 128 / 192 rows, us):
+// 1 sample 7.9 / 11.5 / 18 / 22, 8 samples 19 / 15.4 / 20 / 24, 32 samples
+// 63 / 34 / 32 / 33, 64 samples 113 / 60 / 50 / 43.  192 rows take two channel
+// tiles per wave, which halves the reads of the activations (with one tile
+// per wave 10 % slower there, and no faster on fewer rows).
+extern "C" hipError_t surx_net(const __bf16 *const *wf, const float *const *bias, int mode, const float *params,
+                               const double *n0, void *out, int X, int B, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_to_state, dim3((X * B + 255) / 256), dim3(256), 0, s, out, params, n0, state, X, B);
-    return hipGetLastError();
-}
-
-extern "C" hipError_t surx_unpack(const float *y, float *out, int X, int B, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_unpack, dim3((X * B + 255) / 256), dim3(256), 0, s, y, out, X, B);
-    return hipGetLastError();
+    NetParams np;
+    for (int l = 0; l < 6; ++l) {
+        np.w[l] = wf[l];
+        np.bias[l] = bias[l];
+    }
+    int rows = 0;
+    double best = 0.0;
+    for (int r : {32, 64, 96, 128, 192}) {
+        const long long blocks = (long long)((X + r - NET_HALO - 1) / (r - NET_HALO)) * B;
+        const long long per_cu = (blocks + NET_CUS - 1) / NET_CUS;
+        const double chain = 4.5 + 0.105 * r, work = 5.0 + 0.064 * (double)per_cu * (r + 8);
+        const double t = chain > work ? chain : work;
+        if (!rows || t < best) {
+            rows = r;
+            best = t;
+        }
+    }
+    return rows == 192 ? launch_net<2>(np, mode, params, n0, out, X, B, rows, s)
+                       : launch_net<1>(np, mode, params, n0, out, X, B, rows, s);
 }

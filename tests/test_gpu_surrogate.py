@@ -339,3 +339,43 @@ def test_state_load_batched_and_errors(torch, O):
     assert e.value.code == pic.PIC_ENAN
     with pytest.raises(ValueError):
         pic.Handle(cfgs[0], state=torch.zeros((1, 3, 256), dtype=torch.float64, device="cuda:0"))
+
+
+@pytest.mark.parametrize("B,X", [(1, 64), (2, 128), (9, 320), (20, 704), (70, 64), (5, 4096), (33, 1216), (64, 2048)])
+def test_forward_is_the_same_on_every_tiling(sur, torch, B, X):
+    """Rows per block follow the batch and the length (32 to 192, the last tile
+    ragged); the values do not: a batch equals its samples one at a time, bit
+    for bit, and the densities and the state equal the network's channels
+    converted in float64 (exp within two units in the last place)."""
+    _say("case: forward tilings B=%d X=%d" % (B, X))
+    W, b = presets.surrogate_test_weights(23)
+    net = sur.Surrogate(B, X, device="cuda:0")
+    net.set_weights(W, b)
+    p = torch.tensor(_params(B, 31), dtype=torch.float32, device="cuda:0")
+    n0 = torch.linspace(1e15, 3e16, B, dtype=torch.float64, device="cuda:0")
+    out, dens, state = net.forward(p), net.densities(p, n0), net.state(p, n0)
+    for k in sorted({0, B // 2, B - 1}):
+        assert torch.equal(net.forward(p[k:k + 1])[0], out[k])
+        assert torch.equal(net.state(p[k:k + 1], n0[k:k + 1])[0], state[k])
+    assert torch.equal(dens, state[:, :2])
+    o = out.cpu().numpy().astype(np.float64)
+    v1 = [math.sqrt(1.602176634e-19 / m) for m in (9.1093837015e-31, 6.6464731e-27 - 9.1093837015e-31)]
+    ref = np.concatenate([n0.cpu().numpy()[:, None, None] * np.exp(o[:, 1:3]),
+                          p[:, 2].double().cpu().numpy()[:, None, None] * o[:, 0:1], o[:, 3:21] * v1[0],
+                          o[:, 21:39] * v1[1]], 1)
+    assert np.allclose(state.cpu().numpy(), ref, rtol=1e-15 * 4, atol=0.0)
+
+
+def test_forward_into_an_odd_offset(sur, torch):
+    """The caller's output needs no more than a float's alignment."""
+    _say("case: forward into an output at an odd element offset")
+    W, b = presets.surrogate_test_weights(23)
+    B, X = 3, 192
+    net = sur.Surrogate(B, X, device="cuda:0")
+    net.set_weights(W, b)
+    p = _params(B, 31)
+    ref = net.forward(p)
+    flat = torch.full((B * SO.N_OUT * X + 3,), float("nan"), dtype=torch.float32, device="cuda:0")
+    out = flat[1:1 + B * SO.N_OUT * X].view(B, SO.N_OUT, X)
+    assert torch.equal(net.forward(p, out), ref)
+    assert torch.isnan(flat[:1]).all() and torch.isnan(flat[1 + B * SO.N_OUT * X:]).all()
