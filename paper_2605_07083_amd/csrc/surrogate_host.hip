@@ -1,8 +1,8 @@
 // surrogate_host.hip -- host side of the surrogate C ABI (include/surrogate.h):
 // workspace layout, weight packing, the forward pass into the caller's output
-// (one launch) and the launch sequence of the training step (forward layers,
-// loss, one backward kernel per layer for the input and weight gradients, Adam
-// with re-quantisation).
+// (one launch) and the launch sequence of the training step (forward pass with
+// the loss, one backward kernel per layer for the input and weight gradients,
+// Adam with re-quantisation).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -15,18 +15,19 @@
 #include "../../include/surrogate.h"
 
 extern "C" {
-hipError_t surx_features(const float *params, __bf16 *feat, double *loss0, int X, int B, hipStream_t s);
-hipError_t surx_conv_fwd(int layer, const __bf16 *in, const __bf16 *Wf, const float *bias, float *yf, __bf16 *yb,
-                         int X, int B, hipStream_t s);
-hipError_t surx_loss(const float *out, const float *target, __bf16 *dz, double *loss, int X, int B, hipStream_t s);
+int surx_net_train_blocks(int X, int B);
+hipError_t surx_net_train(const __bf16 *const *wf, const float *const *bias, const float *params, const float *target,
+                          float *const *y, __bf16 *feat, __bf16 *dz, double *loss, int *blocks, int X, int B,
+                          hipStream_t s);
 hipError_t surx_conv_bwd(int layer, const __bf16 *dz, const float *yin, const __bf16 *feat, const __bf16 *Wb,
                          __bf16 *dzprev, float *part, float *pbias, int X, int B, hipStream_t s);
 int surx_wgrad_parts(int X, int B);
-int surx_loss_slots(void);
-hipError_t surx_reduce_adam(const float *part, const float *pbias, int P, float *wm, float *mw, float *vw, float *dw,
-                            float *bias, float *mb, float *vb, float *db, __bf16 *Wf, __bf16 *Wb, int cin, int coutp,
-                            int cout_real, int kp, int kpb, float lr, float b1, float b2, float eps, float c1,
-                            float c2, hipStream_t s);
+hipError_t surx_reduce_adam(const float *const *part, const float *const *pbias, int P, float *const *wm,
+                            float *const *mw, float *const *vw, float *const *dw, float *const *bias,
+                            float *const *mb, float *const *vb, float *const *db, __bf16 *const *Wf,
+                            __bf16 *const *Wb, const int *cin, const int *coutp, const int *cout_real, const int *kp,
+                            const int *kpb, const double *loss_parts, int nloss, double *loss, float lr, float b1,
+                            float b2, float eps, float c1, float c2, hipStream_t s);
 hipError_t surx_requant(const float *wm, __bf16 *Wf, __bf16 *Wb, int cin, int coutp, int cout_real, int kp, int kpb,
                         hipStream_t s);
 hipError_t surx_init_weights(float *wm, int cin, int coutp, int cout_real, int kp, uint32_t layer, uint32_t seed,
@@ -90,12 +91,12 @@ struct sur_net {
     size_t param_bytes = 0;       // weights, moments, grads: the first bytes of ws
     Layer L[SUR_LAYERS];
     __bf16 *feat = nullptr;       // [bmax][X][16]
-    float *yf[SUR_LAYERS];        // [bmax][X][coutp]
-    __bf16 *yb[SUR_LAYERS - 1];   // bf16 copies of the hidden outputs
+    float *y[SUR_LAYERS - 1];     // hidden outputs [bmax][X][64]
     __bf16 *dz[2];                // output gradients of a layer [bmax][X][64], ping-pong
-    float *part = nullptr;        // a layer's partial weight gradients [parts][64][320]
-    float *pbias = nullptr;       // and bias gradients [parts][64]
-    double *loss = nullptr;       // surx_loss_slots() partial sums of the training loss
+    float *part[SUR_LAYERS];      // partial weight gradients [parts][coutp][kp]
+    float *pbias[SUR_LAYERS];     // and bias gradients [parts][coutp]
+    double *loss = nullptr;       // the training loss
+    double *loss_parts = nullptr; // its shares per forward block
     long long t = 0;              // Adam steps taken
 };
 
@@ -123,15 +124,17 @@ void layout(sur_net &n, Bump &bp)
         L.wf = bp.take<__bf16>(nw);
         L.wb = bp.take<__bf16>((size_t)L.cin * L.kpb);
     }
-    n.loss = bp.take<double>((size_t)surx_loss_slots());
+    n.loss = bp.take<double>(1);
     n.param_bytes = bp.off;
     n.feat = bp.take<__bf16>(P * SUR_IN);
-    for (int l = 0; l < SUR_LAYERS; ++l) n.yf[l] = bp.take<float>(P * COUTP[l]);
-    for (int l = 0; l < SUR_LAYERS - 1; ++l) n.yb[l] = bp.take<__bf16>(P * COUTP[l]);
+    for (int l = 0; l < SUR_LAYERS - 1; ++l) n.y[l] = bp.take<float>(P * SUR_HIDDEN);
     for (int k = 0; k < 2; ++k) n.dz[k] = bp.take<__bf16>(P * SUR_HIDDEN);
     const size_t parts = (size_t)surx_wgrad_parts(n.X, n.bmax);
-    n.part = bp.take<float>(parts * SUR_HIDDEN * pad32(SUR_KS * SUR_HIDDEN));
-    n.pbias = bp.take<float>(parts * SUR_HIDDEN);
+    for (int l = 0; l < SUR_LAYERS; ++l) {
+        n.part[l] = bp.take<float>(parts * n.L[l].coutp * n.L[l].kp);
+        n.pbias[l] = bp.take<float>(parts * n.L[l].coutp);
+    }
+    n.loss_parts = bp.take<double>((size_t)surx_net_train_blocks(n.X, n.bmax));
 }
 
 int check_shape(int batch, int cells)
@@ -146,19 +149,6 @@ int requant_all(sur_net *n)
     for (int l = 0; l < SUR_LAYERS; ++l) {
         const Layer &L = n->L[l];
         SUR_TRY(surx_requant(L.wm, L.wf, L.wb, L.cin, L.coutp, L.cout, L.kp, L.kpb, n->stream));
-    }
-    return PIC_OK;
-}
-
-// The training step's forward pass: every layer's output kept for the
-// backward pass; also clears the loss accumulators.
-int forward(sur_net *n, const float *params, int B)
-{
-    SUR_TRY(surx_features(params, n->feat, n->loss, n->X, B, n->stream));
-    for (int l = 0; l < SUR_LAYERS; ++l) {
-        const __bf16 *in = l == 0 ? n->feat : n->yb[l - 1];
-        __bf16 *yb = l < SUR_LAYERS - 1 ? n->yb[l] : nullptr;
-        SUR_TRY(surx_conv_fwd(l, in, n->L[l].wf, n->L[l].bias, n->yf[l], yb, n->X, B, n->stream));
     }
     return PIC_OK;
 }
@@ -327,39 +317,49 @@ int sur_train_step(sur_net *n, const float *dev_params, const float *dev_target,
     if (batch < 1 || batch > n->bmax) return fail(PIC_EINVAL, "batch exceeds the workspace's max_batch");
     if (!(lr > 0.0f)) return fail(PIC_EINVAL, "learning rate must be positive");
     const int X = n->X;
-    // the forward pass zeroes the loss accumulators (features kernel)
-    int rc = forward(n, dev_params, batch);
-    if (rc) return rc;
-    SUR_TRY(surx_loss(n->yf[SUR_LAYERS - 1], dev_target, n->dz[0], n->loss, X, batch, n->stream));
+    const __bf16 *wf[SUR_LAYERS];
+    const float *bias[SUR_LAYERS];
+    for (int l = 0; l < SUR_LAYERS; ++l) {
+        wf[l] = n->L[l].wf;
+        bias[l] = n->L[l].bias;
+    }
+    int shares = 0;
+    SUR_TRY(surx_net_train(wf, bias, dev_params, dev_target, n->y, n->feat, n->dz[0], n->loss_parts, &shares, X,
+                           batch, n->stream));
     n->t += 1;
     const float c1 = (float)(1.0 - std::pow((double)B1, (double)n->t));
     const float c2 = (float)(1.0 - std::pow((double)B2, (double)n->t));
-    const int parts = surx_wgrad_parts(X, batch);
-    // per layer, last to first: the input gradient (with this layer's weights
-    // before their update) and the partial weight gradients in one kernel,
-    // then the layer's gradient summed from the partials, its Adam update and
-    // BF16 copies
+    // per layer, last to first: the input gradient and the partial weight
+    // gradients in one kernel; then every layer's gradient summed from the
+    // partials, its Adam update and BF16 copies in one launch
     int cur = 0;
     for (int l = SUR_LAYERS - 1; l >= 0; --l) {
         const Layer &L = n->L[l];
         if (l > 0)
-            SUR_TRY(surx_conv_bwd(l, n->dz[cur], n->yf[l - 1], nullptr, L.wb, n->dz[cur ^ 1], n->part, n->pbias, X,
-                                  batch, n->stream));
+            SUR_TRY(surx_conv_bwd(l, n->dz[cur], n->y[l - 1], nullptr, L.wb, n->dz[cur ^ 1], n->part[l], n->pbias[l],
+                                  X, batch, n->stream));
         else
-            SUR_TRY(surx_conv_bwd(0, n->dz[cur], nullptr, n->feat, nullptr, nullptr, n->part, n->pbias, X, batch,
-                                  n->stream));
+            SUR_TRY(surx_conv_bwd(0, n->dz[cur], nullptr, n->feat, nullptr, nullptr, n->part[0], n->pbias[0], X,
+                                  batch, n->stream));
         cur ^= 1;
-        SUR_TRY(surx_reduce_adam(n->part, n->pbias, parts, L.wm, L.mw, L.vw, L.dw, L.bias, L.mb, L.vb, L.db, L.wf,
-                                 L.wb, L.cin, L.coutp, L.cout, L.kp, L.kpb, lr, B1, B2, EPS, c1, c2, n->stream));
     }
+    float *wm[SUR_LAYERS], *mw[SUR_LAYERS], *vw[SUR_LAYERS], *dw[SUR_LAYERS];
+    float *bm[SUR_LAYERS], *mb[SUR_LAYERS], *vb[SUR_LAYERS], *db[SUR_LAYERS];
+    __bf16 *lwf[SUR_LAYERS], *lwb[SUR_LAYERS];
+    int kp[SUR_LAYERS], kpb[SUR_LAYERS];
+    for (int l = 0; l < SUR_LAYERS; ++l) {
+        const Layer &L = n->L[l];
+        wm[l] = L.wm; mw[l] = L.mw; vw[l] = L.vw; dw[l] = L.dw;
+        bm[l] = L.bias; mb[l] = L.mb; vb[l] = L.vb; db[l] = L.db;
+        lwf[l] = L.wf; lwb[l] = L.wb;
+        kp[l] = L.kp; kpb[l] = L.kpb;
+    }
+    SUR_TRY(surx_reduce_adam(n->part, n->pbias, surx_wgrad_parts(X, batch), wm, mw, vw, dw, bm, mb, vb, db, lwf, lwb,
+                             CIN, COUTP, COUT, kp, kpb, n->loss_parts, shares, n->loss, lr,
+                             B1, B2, EPS, c1, c2, n->stream));
     if (loss) {
-        std::vector<double> parts((size_t)surx_loss_slots());
-        SUR_TRY(hipMemcpyAsync(parts.data(), n->loss, parts.size() * sizeof(double), hipMemcpyDeviceToHost,
-                               n->stream));
+        SUR_TRY(hipMemcpyAsync(loss, n->loss, sizeof(double), hipMemcpyDeviceToHost, n->stream));
         SUR_TRY(hipStreamSynchronize(n->stream));
-        double sum = 0.0;
-        for (double v : parts) sum += v;
-        *loss = sum;
     }
     return PIC_OK;
 }

@@ -32,8 +32,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int KS = 5;     // kernel size
 constexpr int OUT = 39;   // output channels: phi / V, ln n_e / n0, ln n_i / n0, 36 velocity quantiles
 constexpr int OUTP = 48;  // padded to whole 16-column matrix-core tiles
-constexpr int PAD = 2;
-constexpr int LOSS_SLOTS = 64;   // loss accumulators (see k_loss)
 
 __device__ __forceinline__ bf16x8 zero8()
 {
@@ -107,31 +105,11 @@ __device__ __forceinline__ void features_part(const float *__restrict__ p, int x
     }
 }
 
-__global__ void k_features(const float *__restrict__ params, __bf16 *__restrict__ feat, double *__restrict__ loss0,
-                           int X, int B)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx < LOSS_SLOTS && loss0) loss0[idx] = 0.0;     // the training step's loss accumulators
-    if (idx >= X * B) return;
-    const int b = idx / X, x = idx - b * X;
-    __bf16 f[16];
-    features_part<0>(params + 4 * b, x, X, f);
-    features_part<1>(params + 4 * b, x, X, f);
-    features_part<2>(params + 4 * b, x, X, f);
-    features_part<3>(params + 4 * b, x, X, f);
-    __bf16 *o = feat + (size_t)idx * 16;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) o[c] = f[c];
-}
-
 // ---------------------------------------------------------------------------
 // Weights of a layer staged in LDS once per block: rows of the padded K
 // length plus 8 elements, so that the 16 rows one matrix-core fragment reads
 // fall on different banks.
 // ---------------------------------------------------------------------------
-constexpr int BLOCK_POS = 256;   // positions per block of the forward and input-gradient kernels
-constexpr int CONV_THREADS = 512;    // 8 waves: two 16-position tiles each
-
 template <int ROWS, int KP, int THREADS>
 __device__ __forceinline__ void stage_rows(__bf16 *lds, const __bf16 *__restrict__ src)
 {
@@ -147,213 +125,6 @@ __device__ __forceinline__ void stage_rows(__bf16 *lds, const __bf16 *__restrict
     for (int k = 0; k < N; ++k) {
         const int v = threadIdx.x + k * THREADS;
         if (v < ROWS * V) *reinterpret_cast<bf16x8 *>(lds + (v / V) * (KP + 8) + (v % V) * 8) = r[k];
-    }
-}
-
-// A layer's forward weights, already in fragment order, copied as they are.
-template <int N, int THREADS>
-__device__ __forceinline__ void stage_frags(__bf16 *lds, const __bf16 *__restrict__ src)
-{
-    constexpr int PER = (N / 8 + THREADS - 1) / THREADS;
-    bf16x8 r[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int v = threadIdx.x + k * THREADS;
-        r[k] = v < N / 8 ? load8(src + v * 8) : zero8();
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int v = threadIdx.x + k * THREADS;
-        if (v < N / 8) *reinterpret_cast<bf16x8 *>(lds + v * 8) = r[k];
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Forward conv: out[b][x][co] = act(bias[co] + sum_{t, ci} W[co][t][ci] in[b][x+t-2][ci]).
-// GEMM M = positions, N = COUT, K = 5*CIN (padded to KP).  A block of 8
-// waves covers BLOCK_POS positions of one sample: the layer's weights and the
-// block's input rows (two halo positions each side, zero outside the sample)
-// are staged in LDS with one batch of loads; a wave computes 16 positions x
-// COUT at a time from LDS and writes its tile through LDS as whole rows
-// (16-byte stores of the FP32 output and its bfloat16 copy).  The input row
-// stride puts 8 consecutive rows on different 16-byte bank groups.
-// ---------------------------------------------------------------------------
-constexpr int FW_ROWS = BLOCK_POS + 4;
-constexpr int fw_in_stride(int c) { return c == 64 ? 72 : 24; }     // 144 or 48 bytes per row
-
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
-template <int CIN, int COUT, bool TANH>
-__global__ __launch_bounds__(CONV_THREADS) void k_conv_fwd(const __bf16 *__restrict__ in, const __bf16 *__restrict__ Wf,
-                                                  const float *__restrict__ bias, float *__restrict__ yf,
-                                                  __bf16 *__restrict__ yb, int X, int B)
-{
-    constexpr int K = KS * CIN;
-    constexpr int KP = (K + 31) / 32 * 32;
-    constexpr int NT = COUT / 16;
-    constexpr int SIN = fw_in_stride(CIN);
-    constexpr int IV = CIN / 8;                                  // 16-byte vectors per input row
-    constexpr int NI = (FW_ROWS * IV + CONV_THREADS - 1) / CONV_THREADS;
-    constexpr int OS = COUT + 4;                                 // staged output row (floats)
-    static_assert(CIN == 16 || CIN == 64, "input row stride");
-    __shared__ __align__(16) __bf16 wl[COUT * KP];
-    __shared__ __align__(16) __bf16 it[FW_ROWS * SIN];
-    __shared__ __align__(16) float ot[CONV_THREADS / 64][16 * OS];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int tiles = (X + BLOCK_POS - 1) / BLOCK_POS;
-    const int b = blockIdx.x / tiles;
-    if (b >= B) return;
-    const int xb = (blockIdx.x - b * tiles) * BLOCK_POS;
-    const __bf16 *inb = in + (size_t)b * X * CIN;
-    {
-        bf16x8 r[NI];
-#pragma unroll
-        for (int k = 0; k < NI; ++k) {
-            const int v = threadIdx.x + k * CONV_THREADS, x = xb - PAD + v / IV;
-            r[k] = v < FW_ROWS * IV && x >= 0 && x < X ? load8(inb + (size_t)x * CIN + (v % IV) * 8) : zero8();
-        }
-        stage_frags<COUT * KP, CONV_THREADS>(wl, Wf);
-#pragma unroll
-        for (int k = 0; k < NI; ++k) {
-            const int v = threadIdx.x + k * CONV_THREADS;
-            if (v < FW_ROWS * IV) *reinterpret_cast<bf16x8 *>(it + (v / IV) * SIN + (v % IV) * 8) = r[k];
-        }
-    }
-    __syncthreads();
-    const int m = lane & 15, kb = lane >> 4;
-    float *o = ot[w];
-    for (int x0 = xb + w * 16; x0 < min(X, xb + BLOCK_POS); x0 += CONV_THREADS / 4) {
-        f32x4 acc[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KP / 32; ++ks) {
-            const int kappa = ks * 32 + kb * 8;
-            bf16x8 a = zero8();
-            if (kappa < K) {
-                // in at position x0 + m + t - 2: row x0 - xb + m + t of the staged rows
-                const int t = kappa / CIN, ci = kappa - t * CIN;
-                a = *reinterpret_cast<const bf16x8 *>(it + (x0 - xb + m + t) * SIN + ci);
-            }
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const bf16x8 bw = load8(wl + ((nt * (KP / 32) + ks) * 64 + lane) * 8);
-                acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw, acc[nt], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int co = nt * 16 + m;
-            const float bc = bias[co];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float v = acc[nt][i] + bc;
-                if (TANH) v = tanhf(v);
-                o[(kb * 4 + i) * OS + co] = v;
-            }
-        }
-        wave_lds_sync();
-        // the tile's 16 rows are contiguous in yf and yb
-        float *yrow = yf + ((size_t)b * X + x0) * COUT;
-        constexpr int Q4 = 16 * COUT / 4;
-#pragma unroll
-        for (int k = 0; k < (Q4 + 63) / 64; ++k) {
-            const int e = lane + 64 * k;
-            if (e < Q4) {
-                const int r = e / (COUT / 4), c = (e % (COUT / 4)) * 4;
-                *reinterpret_cast<float4 *>(yrow + r * COUT + c) = *reinterpret_cast<const float4 *>(o + r * OS + c);
-            }
-        }
-        if (yb) {
-            __bf16 *brow = yb + ((size_t)b * X + x0) * COUT;
-            constexpr int Q8 = 16 * COUT / 8;
-#pragma unroll
-            for (int k = 0; k < (Q8 + 63) / 64; ++k) {
-                const int e = lane + 64 * k;
-                if (e < Q8) {
-                    const int r = e / (COUT / 8), c = (e % (COUT / 8)) * 8;
-                    bf16x8 h;
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) h[u] = (__bf16)o[r * OS + c + u];
-                    *reinterpret_cast<bf16x8 *>(brow + r * COUT + c) = h;
-                }
-            }
-        }
-        wave_lds_sync();
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Loss: mean over (b, channel < OUT, x) of (out - target)^2.  Writes
-// dZ = 2 (out - target) / count as BF16 in the padded OUTP-channel layout,
-// channels last.  target[b][c][x], out[b][x][OUTP].  A block takes 64
-// positions of one sample: the output tile is read whole into LDS, the target
-// rows along x, and dZ is written along c.
-// Each block adds its sum to one of LOSS_SLOTS accumulators (block % slots),
-// so that a thousand blocks do not queue on one address; the host adds them.
-// ---------------------------------------------------------------------------
-constexpr int LOSS_POS = 64;
-
-__global__ __launch_bounds__(256) void k_loss(const float *__restrict__ out, const float *__restrict__ target,
-                                              __bf16 *__restrict__ dz, double *__restrict__ loss, int X, int B)
-{
-    __shared__ float so[LOSS_POS][OUTP + 1];
-    __shared__ double red[4];
-    const int tiles = X / LOSS_POS;
-    const int b = blockIdx.x / tiles;
-    if (b >= B) return;
-    const int x0 = (blockIdx.x - b * tiles) * LOSS_POS;
-    const int tid = threadIdx.x;
-    const double inv = 1.0 / ((double)OUT * (double)X * (double)B);
-    constexpr int PER = LOSS_POS * OUTP / 256;      // elements per thread, every load issued up front
-    static_assert(LOSS_POS * OUTP % 256 == 0, "whole passes");
-    const float *ob = out + ((size_t)b * X + x0) * OUTP;
-    float r[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) r[k] = ob[tid + 256 * k];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = tid + 256 * k;
-        so[e / OUTP][e % OUTP] = r[k];
-    }
-    // target rows along x (channels 0 .. OUT-1)
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = tid + 256 * k, c = e / LOSS_POS, x = e % LOSS_POS;
-        r[k] = c < OUT ? target[((size_t)b * OUT + c) * X + x0 + x] : 0.0f;
-    }
-    __syncthreads();
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = tid + 256 * k, c = e / LOSS_POS, x = e % LOSS_POS;
-        float g = 0.0f;
-        if (c < OUT) {
-            const float d = so[x][c] - r[k];
-            acc += (double)d * d;
-            g = (float)(2.0 * inv) * d;
-        }
-        so[x][c] = g;
-    }
-    __syncthreads();
-    __bf16 *db = dz + ((size_t)b * X + x0) * OUTP;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = tid + 256 * k;
-        db[e] = (__bf16)so[e / OUTP][e % OUTP];
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if ((tid & 63) == 0) red[tid >> 6] = acc;
-    __syncthreads();
-    if (tid == 0) {
-        const double t = (red[0] + red[1]) + (red[2] + red[3]);
-        if (t != 0.0) atomicAdd(loss + blockIdx.x % LOSS_SLOTS, t * inv);
     }
 }
 
@@ -690,27 +461,58 @@ __global__ __launch_bounds__(BW_THREADS) void k_conv_bwd(const __bf16 *__restric
     }
 }
 
-// The gradient of one layer from its partials, then Adam on the FP32 master
-// weights and biases and the BF16 copies of the weights: forward Wf in
+// ---------------------------------------------------------------------------
+// The gradients of every layer from their partials, then Adam on the FP32
+// master weights and biases and the BF16 copies of the weights: forward Wf in
 // fragment order and transposed Wb[ci][t*COUTP + co].  A block takes 64
-// consecutive entries of the padded weights [COUTP][KP] followed by the
-// biases; wave w sums the partials w, w + 16, ... of each, and the first
-// wave adds the 16 sums in wave order and updates.
+// consecutive entries of a layer's padded weights [COUTP][KP] followed by its
+// biases; wave w sums the partials w, w + 16, ... of each, and the first wave
+// adds the 16 sums in wave order and updates.  One launch for all layers (6 x
+// 5.5 us as a launch per layer, whose few hundred blocks each left the chip
+// half empty).  One more block adds the loss from the forward blocks' shares.
 // ---------------------------------------------------------------------------
 constexpr int RA_WAVES = 16;
 
-__global__ __launch_bounds__(RA_WAVES * 64) void k_reduce_adam(
-    const float *__restrict__ part, const float *__restrict__ pbias, int P, float *__restrict__ wm,
-    float *__restrict__ mw, float *__restrict__ vw, float *__restrict__ dw, float *__restrict__ bias,
-    float *__restrict__ mb, float *__restrict__ vb, float *__restrict__ db, __bf16 *__restrict__ Wf,
-    __bf16 *__restrict__ Wb, int cin, int coutp, int cout_real, int kp, int kpb, float lr, float b1, float b2,
-    float eps, float c1, float c2)
+struct AdamLayer {
+    const float *part, *pbias;
+    float *wm, *mw, *vw, *dw, *bias, *mb, *vb, *db;
+    __bf16 *Wf, *Wb;
+    int cin, coutp, cout_real, kp, kpb;
+    int first;               // the layer's first block
+};
+
+struct AdamArgs {
+    AdamLayer L[6];
+    int P;                   // partials per layer
+    int blocks;              // of all layers
+    const double *loss_parts;
+    int nloss;
+    double *loss;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+__global__ __launch_bounds__(RA_WAVES * 64) void k_reduce_adam(AdamArgs A)
 {
     __shared__ float red[RA_WAVES][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + lane;
-    const int nw = coutp * kp;
-    const bool isw = i < nw, inr = i < nw + coutp;
+    if ((int)blockIdx.x == A.blocks) {
+        if (w != 0) return;
+        double sum = 0.0;
+        for (int k = lane; k < A.nloss; k += 64) sum += A.loss_parts[k];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if (lane == 0) *A.loss = sum;
+        return;
+    }
+    int l = 0;
+#pragma unroll
+    for (int k = 1; k < 6; ++k)
+        if ((int)blockIdx.x >= A.L[k].first) l = k;
+    const AdamLayer &L = A.L[l];
+    const int kp = L.kp, coutp = L.coutp, cin = L.cin;
+    const int i0 = ((int)blockIdx.x - L.first) * 64, i = i0 + lane;
+    const int nw = coutp * kp;                 // a multiple of 64: a block holds weights or biases
+    const bool isw = i0 < nw, inr = i < nw + coutp;
     int co, kappa = 0, stride, at;
     if (isw) {
         co = i / kp;
@@ -722,12 +524,12 @@ __global__ __launch_bounds__(RA_WAVES * 64) void k_reduce_adam(
         stride = coutp;
         at = co;
     }
-    const bool live = inr && co < cout_real && (!isw || kappa < KS * cin);
+    const bool live = inr && co < L.cout_real && (!isw || kappa < KS * cin);
     float sum = 0.0f;
     if (live) {
-        const float *src = (isw ? part : pbias) + at;
+        const float *src = (isw ? L.part : L.pbias) + at;
 #pragma unroll 4
-        for (int q = w; q < P; q += RA_WAVES) sum += src[(size_t)q * stride];
+        for (int q = w; q < A.P; q += RA_WAVES) sum += src[(size_t)q * stride];
     }
     red[w][lane] = sum;
     __syncthreads();
@@ -735,20 +537,20 @@ __global__ __launch_bounds__(RA_WAVES * 64) void k_reduce_adam(
     float gi = 0.0f;
 #pragma unroll
     for (int k = 0; k < RA_WAVES; ++k) gi += red[k][lane];
-    float *wp = isw ? wm + i : bias + co, *mo = isw ? mw + i : mb + co, *ve = isw ? vw + i : vb + co;
-    (isw ? dw[i] : db[co]) = gi;
-    const float m1 = b1 * *mo + (1.0f - b1) * gi;
-    const float v1 = b2 * *ve + (1.0f - b2) * gi * gi;
+    float *wp = isw ? L.wm + i : L.bias + co, *mo = isw ? L.mw + i : L.mb + co, *ve = isw ? L.vw + i : L.vb + co;
+    (isw ? L.dw[i] : L.db[co]) = gi;
+    const float m1 = __builtin_fmaf(1.0f - A.b1, gi, A.b1 * *mo);
+    const float v1 = __builtin_fmaf(gi, (1.0f - A.b2) * gi, A.b2 * *ve);
     *mo = m1;
     *ve = v1;
-    const float nwv = *wp - lr * (m1 / c1) / (sqrtf(v1 / c2) + eps);
+    const float nwv = *wp - A.lr * (m1 / A.c1) / (sqrtf(v1 / A.c2) + A.eps);
     *wp = nwv;
     if (isw) {
         const __bf16 v = (__bf16)(live ? nwv : 0.0f);
-        Wf[frag_at(co, kappa, kp)] = v;
+        L.Wf[frag_at(co, kappa, kp)] = v;
         if (kappa < KS * cin) {
             const int t = kappa / cin, ci = kappa - t * cin;
-            Wb[(size_t)ci * kpb + t * coutp + co] = v;
+            L.Wb[(size_t)ci * L.kpb + t * coutp + co] = v;
         }
     }
 }
@@ -868,7 +670,17 @@ __device__ __forceinline__ void tanh4_settle(f32x4 x, uint2 open, uint2 &h)
 typedef float out_f32x4 __attribute__((__vector_size__(16), aligned(4)));
 typedef double out_f64x2 __attribute__((__vector_size__(16), aligned(8)));
 
-enum NetOut { NET_OUT, NET_DENSITIES, NET_STATE };
+enum NetOut { NET_OUT, NET_DENSITIES, NET_STATE, NET_TRAIN };
+
+// What the training step's forward pass keeps and computes besides.
+struct NetTrain {
+    float *y[5];             // tanh outputs of the hidden layers [b][x][64] (FP32, for the tanh derivative)
+    __bf16 *feat;            // [b][x][16]
+    const float *target;     // [b][39][x]
+    __bf16 *dz;              // gradient of the loss at the output [b][x][48]
+    double *loss;            // per block, its share of the loss
+    int B;
+};
 
 constexpr int NET_THREADS = 256;
 constexpr int NET_HALO = 20;     // rows beyond the block's outputs, both sides together
@@ -876,9 +688,9 @@ constexpr int NET_HALO = 20;     // rows beyond the block's outputs, both sides 
 // rows: a multiple of 16 C PB; grid (tiles x samples); LDS 2 (rows + 4) x 64
 // bfloat16 and 6 x 64 biases.
 template <int C, int MODE>
-__global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const float *__restrict__ params,
-                                                        const double *__restrict__ n0, void *__restrict__ outp, int X,
-                                                        int tiles, int T, int rows)
+__device__ __forceinline__ void net_block(const NetParams &np, const float *__restrict__ params,
+                                          const double *__restrict__ n0, void *__restrict__ outp, const NetTrain &tr,
+                                          int X, int tiles, int T, int rows)
 {
     extern __shared__ __align__(16) __bf16 net_lds[];
     constexpr int FS = 24;                         // feature row stride (48 bytes)
@@ -891,6 +703,7 @@ __global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const floa
     const int cg = w % (4 / C), rw = w / (4 / C) * (G * PB * 16);  // this wave's channel tiles and first row
     const int b = blockIdx.x / tiles;
     const int x0 = (blockIdx.x - b * tiles) * T;
+    const int x1 = min(X, x0 + T);                 // the block's own positions: [x0, x1)
     const float *pb = params + (size_t)b * 4;
 
     bf16x8 W[C][10];                               // a layer's weights
@@ -928,6 +741,8 @@ __global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const floa
                 if (of == PART) {
                     const bf16x2 v = {f[2 * c], f[2 * c + 1]};
                     o[c] = __builtin_bit_cast(uint32_t, v);
+                    if (MODE == NET_TRAIN && x >= x0 && x < x1)
+                        *reinterpret_cast<bf16x2 *>(tr.feat + ((size_t)b * X + x) * 16 + 2 * c) = v;
                 }
             }
         }
@@ -962,22 +777,35 @@ __global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const floa
         const int q = m + 2, g = (cg * C + c) * 2 + (kb >> 1);
         put[c] = q * 64 + ((g ^ (q & 7)) << 3) + (kb & 1) * 4;
     }
-    auto activation = [&](__bf16 *dst, const f32x4 (&acc)[C][PB], int r0) {
+    auto activation = [&](int l, __bf16 *dst, const f32x4 (&acc)[C][PB], int r0) {
         __bf16 *row = dst + r0 * 64;
 #pragma unroll
         for (int p = 0; p < PB; ++p) {
-            uint2 h[C], open[C];
-            uint32_t any = 0;
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                h[c] = tanh4(acc[c][p] + bias[c], open[c]);
-                any |= open[c].x | open[c].y;
-            }
-            if (__builtin_expect(__any(any), 0)) {
-#pragma unroll
-                for (int c = 0; c < C; ++c) tanh4_settle(acc[c][p] + bias[c], open[c], h[c]);
-            }
             const int x = x0 - 10 + r0 + p * 16 + m;
+            uint2 h[C];
+            if constexpr (MODE == NET_TRAIN) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    f32x4 y = acc[c][p] + bias[c];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) y[i] = tanhf(y[i]);
+                    h[c] = make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
+                    if (x >= x0 && x < x1)
+                        *reinterpret_cast<f32x4 *>(tr.y[l] + ((size_t)b * X + x) * 64 + (cg * C + c) * 16 + kb * 4) = y;
+                }
+            } else {
+                uint2 open[C];
+                uint32_t any = 0;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    h[c] = tanh4(acc[c][p] + bias[c], open[c]);
+                    any |= open[c].x | open[c].y;
+                }
+                if (__builtin_expect(__any(any), 0)) {
+#pragma unroll
+                    for (int c = 0; c < C; ++c) tanh4_settle(acc[c][p] + bias[c], open[c], h[c]);
+                }
+            }
             if (!inside && (x < 0 || x >= X)) {
 #pragma unroll
                 for (int c = 0; c < C; ++c) h[c] = make_uint2(0u, 0u);
@@ -1042,12 +870,12 @@ __global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const floa
 #pragma unroll 1
     for (int g = 0; g < groups - 1; ++g) {
         first_products(rw + g * PB * 16);
-        activation(net_lds, acc, rw + g * PB * 16);
+        activation(0, net_lds, acc, rw + g * PB * 16);
     }
     const int last = rw + max(groups - 1, 0) * PB * 16;      // the wave's last group
     first_products(last);
     load_weights(1, K10{});
-    activation(net_lds, acc, last);
+    activation(0, net_lds, acc, last);
     __syncthreads();
 #pragma unroll 1
     for (int l = 1; l < 5; ++l) {
@@ -1057,16 +885,18 @@ __global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const floa
 #pragma unroll 1
         for (int g = 0; g < groups - 1; ++g) {
             products(src, rw + g * PB * 16);
-            activation(dst, acc, rw + g * PB * 16);
+            activation(l, dst, acc, rw + g * PB * 16);
         }
         products(src, last);
         load_weights(l + 1, K10{});      // their registers are free: the next layer's, beside the activation
-        activation(dst, acc, last);
+        activation(l, dst, acc, last);
         __syncthreads();
     }
     // the last layer: row s is output position x0 + s, its inputs rows s + 10 .. s + 14
 #pragma unroll
     for (int ks = 0; ks < 10; ++ks) off[ks] = group(10, ks);
+    const double inv = MODE == NET_TRAIN ? 1.0 / ((double)OUT * (double)X * (double)tr.B) : 0.0;
+    double sq = 0.0;                     // training: the lane's sum of (out - target)^2
 #pragma unroll 1
     for (int g = 0; g < G; ++g) {
         const int s0 = rw + g * PB * 16;
@@ -1083,9 +913,40 @@ __global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const floa
                 const bf16x8 a = load8(net_lds + (s0 + p * 16) * 64 + off[ks]);
 #pragma unroll
                 for (int c = 0; c < C; ++c)
-                    if (cg * C + c < OUTP / 16)
-                        acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, W[c][ks], acc[c][p], 0, 0, 0);
+                    if (cg * C + c < OUTP / 16) {
+                        if constexpr (MODE == NET_TRAIN)     // four channels of a position per lane, as dz is laid out
+                            acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[c][ks], a, acc[c][p], 0, 0, 0);
+                        else
+                            acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, W[c][ks], acc[c][p], 0, 0, 0);
+                    }
             }
+        }
+        if constexpr (MODE == NET_TRAIN) {
+            // dz = 2 (out - target) / count in bfloat16, zero in the padding channels
+#pragma unroll
+            for (int p = 0; p < PB; ++p) {
+                const int s = s0 + p * 16 + m, x = x0 + s;
+                if (s >= T || x >= X) continue;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const int co = (cg * C + c) * 16 + kb * 4;
+                    if (co >= OUTP) continue;
+                    float dg[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        dg[i] = 0.0f;
+                        if (co + i < OUT) {
+                            const float d = acc[c][p][i] + bias_lds[5 * 64 + co + i] -
+                                            tr.target[((size_t)b * OUT + co + i) * X + x];
+                            sq += (double)d * d;
+                            dg[i] = (float)(2.0 * inv) * d;
+                        }
+                    }
+                    *reinterpret_cast<uint2 *>(tr.dz + ((size_t)b * X + x) * OUTP + co) =
+                        make_uint2(pack_bf16(dg[0], dg[1]), pack_bf16(dg[2], dg[3]));
+                }
+            }
+            continue;
         }
 #pragma unroll
         for (int p = 0; p < PB; ++p) {
@@ -1125,7 +986,35 @@ __global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const floa
             }
         }
     }
+    if constexpr (MODE == NET_TRAIN) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+        __syncthreads();                 // the biases' place is free
+        double *red = reinterpret_cast<double *>(bias_lds);
+        if (lane == 0) red[w] = sq;
+        __syncthreads();
+        if (threadIdx.x == 0) tr.loss[blockIdx.x] = ((red[0] + red[1]) + (red[2] + red[3])) * inv;
+    }
 }
+
+template <int C, int MODE>
+__global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const float *__restrict__ params,
+                                                        const double *__restrict__ n0, void *__restrict__ outp, int X,
+                                                        int tiles, int T, int rows)
+{
+    net_block<C, MODE>(np, params, n0, outp, NetTrain{}, X, tiles, T, rows);
+}
+
+// The training step's forward pass.  Bound by the vector unit: the FP32 hidden
+// outputs, kept for the backward pass, take tanhf itself (13 us of 50 at 32
+// samples x 2048 cells; storing them 3).  With the loss inside it takes the
+// place of eight launches: 83 us, every activation written twice and read once.
+__global__ __launch_bounds__(NET_THREADS, 3) void k_net_train(NetParams np, const float *__restrict__ params,
+                                                              NetTrain tr, int X, int tiles, int T, int rows)
+{
+    net_block<1, NET_TRAIN>(np, params, nullptr, nullptr, tr, X, tiles, T, rows);
+}
+
 
 }  // namespace sur
 
@@ -1133,33 +1022,6 @@ __global__ __launch_bounds__(NET_THREADS, 3) void k_net(NetParams np, const floa
 // Launch wrappers
 // ---------------------------------------------------------------------------
 using namespace sur;
-
-extern "C" int surx_loss_slots(void) { return LOSS_SLOTS; }
-
-// loss0 (LOSS_SLOTS doubles, may be null) is cleared for the training step's loss
-extern "C" hipError_t surx_features(const float *params, __bf16 *feat, double *loss0, int X, int B, hipStream_t s)
-{
-    const int n = X * B > LOSS_SLOTS ? X * B : LOSS_SLOTS;
-    hipLaunchKernelGGL(k_features, dim3((n + 255) / 256), dim3(256), 0, s, params, feat, loss0, X, B);
-    return hipGetLastError();
-}
-
-extern "C" hipError_t surx_conv_fwd(int layer, const __bf16 *in, const __bf16 *Wf, const float *bias, float *yf,
-                                    __bf16 *yb, int X, int B, hipStream_t s)
-{
-    dim3 g((X + BLOCK_POS - 1) / BLOCK_POS * B), t(CONV_THREADS);
-    if (layer == 0) hipLaunchKernelGGL((k_conv_fwd<16, 64, true>), g, t, 0, s, in, Wf, bias, yf, yb, X, B);
-    else if (layer < 5) hipLaunchKernelGGL((k_conv_fwd<64, 64, true>), g, t, 0, s, in, Wf, bias, yf, yb, X, B);
-    else hipLaunchKernelGGL((k_conv_fwd<64, OUTP, false>), g, t, 0, s, in, Wf, bias, yf, yb, X, B);
-    return hipGetLastError();
-}
-
-extern "C" hipError_t surx_loss(const float *out, const float *target, __bf16 *dz, double *loss, int X, int B,
-                                hipStream_t s)
-{
-    hipLaunchKernelGGL(k_loss, dim3(X / LOSS_POS * B), dim3(256), 0, s, out, target, dz, loss, X, B);
-    return hipGetLastError();
-}
 
 // backward pass of layer `layer` (grid: batch x slices): layers 1..5 take the
 // FP32 input y (the layer below's output) and write the layer below's output
@@ -1180,14 +1042,35 @@ extern "C" hipError_t surx_conv_bwd(int layer, const __bf16 *dz, const float *yi
 
 extern "C" int surx_wgrad_parts(int X, int B) { return B * ((X + BW_SLICE - 1) / BW_SLICE); }
 
-extern "C" hipError_t surx_reduce_adam(const float *part, const float *pbias, int P, float *wm, float *mw, float *vw,
-                                       float *dw, float *bias, float *mb, float *vb, float *db, __bf16 *Wf, __bf16 *Wb,
-                                       int cin, int coutp, int cout_real, int kp, int kpb, float lr, float b1,
-                                       float b2, float eps, float c1, float c2, hipStream_t s)
+// Adam over every layer (the fields of AdamLayer but `first`, per layer) and
+// the loss from the forward blocks' shares.
+extern "C" hipError_t surx_reduce_adam(const float *const *part, const float *const *pbias, int P, float *const *wm,
+                                       float *const *mw, float *const *vw, float *const *dw, float *const *bias,
+                                       float *const *mb, float *const *vb, float *const *db, __bf16 *const *Wf,
+                                       __bf16 *const *Wb, const int *cin, const int *coutp, const int *cout_real,
+                                       const int *kp, const int *kpb, const double *loss_parts, int nloss,
+                                       double *loss, float lr, float b1, float b2, float eps, float c1, float c2,
+                                       hipStream_t s)
 {
-    const int n = coutp * kp + coutp;
-    hipLaunchKernelGGL(k_reduce_adam, dim3((n + 63) / 64), dim3(RA_WAVES * 64), 0, s, part, pbias, P, wm, mw, vw, dw, bias,
-                       mb, vb, db, Wf, Wb, cin, coutp, cout_real, kp, kpb, lr, b1, b2, eps, c1, c2);
+    AdamArgs A;
+    int blocks = 0;
+    for (int l = 0; l < 6; ++l) {
+        A.L[l] = AdamLayer{part[l], pbias[l], wm[l], mw[l], vw[l], dw[l], bias[l], mb[l], vb[l], db[l], Wf[l], Wb[l],
+                           cin[l], coutp[l], cout_real[l], kp[l], kpb[l], blocks};
+        blocks += (coutp[l] * kp[l] + coutp[l] + 63) / 64;
+    }
+    A.P = P;
+    A.blocks = blocks;
+    A.loss_parts = loss_parts;
+    A.nloss = nloss;
+    A.loss = loss;
+    A.lr = lr;
+    A.b1 = b1;
+    A.b2 = b2;
+    A.eps = eps;
+    A.c1 = c1;
+    A.c2 = c2;
+    hipLaunchKernelGGL(k_reduce_adam, dim3(blocks + 1), dim3(RA_WAVES * 64), 0, s, A);
     return hipGetLastError();
 }
 
@@ -1210,45 +1093,20 @@ extern "C" hipError_t surx_init_weights(float *wm, int cin, int coutp, int cout_
 
 constexpr int NET_CUS = 256;
 
-template <int C>
-static hipError_t launch_net(const NetParams &np, int mode, const float *params, const double *n0, void *out, int X,
-                             int B, int rows, hipStream_t s)
+// Rows per block of a network launch, at most `most`: few rows give many short
+// blocks, but 20 of them are halo computed again by the neighbours.  A call
+// takes about the longer of a block's chain of layers, 4.5 us + 0.105 us a
+// row, and the work of the most loaded CU, 5 us + 0.064 us x (rows + 8) x its
+// blocks; the rows with the least of it are taken.  Measured on the forward
+// pass (2048 cells; 32 / 64 / 128 / 192 rows, us): 1 sample 7.9 / 11.5 / 18 /
+// 22, 8 samples 19 / 15.4 / 20 / 24, 32 samples 63 / 34 / 32 / 33, 64 samples
+// 113 / 60 / 50 / 43.
+static int net_rows(int X, int B, int most)
 {
-    const int most = rows - NET_HALO;
-    // equal tiles, a multiple of 4 positions each
-    const int tiles = (X + most - 1) / most, T = ((X + tiles - 1) / tiles + 3) / 4 * 4;
-    const dim3 g((unsigned)tiles * (unsigned)B), t(NET_THREADS);
-    const size_t lds = (size_t)2 * (rows + 4) * 64 * sizeof(__bf16) + 6 * 64 * sizeof(float);
-    auto *kernel = mode == NET_OUT ? k_net<C, NET_OUT> : mode == NET_DENSITIES ? k_net<C, NET_DENSITIES>
-                                                                              : k_net<C, NET_STATE>;
-    hipLaunchKernelGGL(kernel, g, t, lds, s, np, params, n0, out, X, tiles, T, rows);
-    return hipGetLastError();
-}
-
-// Forward pass of B samples into the caller's output: mode 0 the network's
-// channels [b][39][x] (float), 1 densities [b][2][x], 2 the loader's state
-// [b][39][x] (double; n0 per sample).
-//
-// Rows per block: few rows give many short blocks, but 20 of them are halo
-// computed again by the neighbours.  A call takes about the longer of a
-// block's chain of layers, 4.5 us + 0.105 us a row, and the work of the most
-// loaded CU, 5 us + 0.064 us x (rows + 8) x its blocks; the rows with the
-// least of it are taken.  Measured (2048 cells; 32 / 64 / 128 / 192 rows, us):
-// 1 sample 7.9 / 11.5 / 18 / 22, 8 samples 19 / 15.4 / 20 / 24, 32 samples
-// 63 / 34 / 32 / 33, 64 samples 113 / 60 / 50 / 43.  192 rows take two channel
-// tiles per wave, which halves the reads of the activations (with one tile
-// per wave 10 % slower there, and no faster on fewer rows).
-extern "C" hipError_t surx_net(const __bf16 *const *wf, const float *const *bias, int mode, const float *params,
-                               const double *n0, void *out, int X, int B, hipStream_t s)
-{
-    NetParams np;
-    for (int l = 0; l < 6; ++l) {
-        np.w[l] = wf[l];
-        np.bias[l] = bias[l];
-    }
     int rows = 0;
     double best = 0.0;
     for (int r : {32, 64, 96, 128, 192}) {
+        if (r > most) break;
         const long long blocks = (long long)((X + r - NET_HALO - 1) / (r - NET_HALO)) * B;
         const long long per_cu = (blocks + NET_CUS - 1) / NET_CUS;
         const double chain = 4.5 + 0.105 * r, work = 5.0 + 0.064 * (double)per_cu * (r + 8);
@@ -1258,6 +1116,82 @@ extern "C" hipError_t surx_net(const __bf16 *const *wf, const float *const *bias
             best = t;
         }
     }
-    return rows == 192 ? launch_net<2>(np, mode, params, n0, out, X, B, rows, s)
-                       : launch_net<1>(np, mode, params, n0, out, X, B, rows, s);
+    return rows;
+}
+
+struct NetShape {
+    int rows, tiles, T;
+    unsigned grid;
+    size_t lds;
+};
+
+static NetShape net_shape(int X, int B, int rows)
+{
+    NetShape n;
+    n.rows = rows;
+    // equal tiles, a multiple of 4 positions each
+    n.tiles = (X + rows - NET_HALO - 1) / (rows - NET_HALO);
+    n.T = ((X + n.tiles - 1) / n.tiles + 3) / 4 * 4;
+    n.grid = (unsigned)n.tiles * (unsigned)B;
+    n.lds = (size_t)2 * (rows + 4) * 64 * sizeof(__bf16) + 6 * 64 * sizeof(float);
+    return n;
+}
+
+static NetParams net_params(const __bf16 *const *wf, const float *const *bias)
+{
+    NetParams np;
+    for (int l = 0; l < 6; ++l) {
+        np.w[l] = wf[l];
+        np.bias[l] = bias[l];
+    }
+    return np;
+}
+
+template <int C>
+static hipError_t launch_net(const NetParams &np, int mode, const float *params, const double *n0, void *out, int X,
+                             const NetShape &n, hipStream_t s)
+{
+    auto *kernel = mode == NET_OUT ? k_net<C, NET_OUT> : mode == NET_DENSITIES ? k_net<C, NET_DENSITIES>
+                                                                              : k_net<C, NET_STATE>;
+    hipLaunchKernelGGL(kernel, dim3(n.grid), dim3(NET_THREADS), n.lds, s, np, params, n0, out, X, n.tiles, n.T, n.rows);
+    return hipGetLastError();
+}
+
+// Forward pass of B samples into the caller's output: mode 0 the network's
+// channels [b][39][x] (float), 1 densities [b][2][x], 2 the loader's state
+// [b][39][x] (double; n0 per sample).  192 rows take two channel tiles per
+// wave, which halves the reads of the activations (with one tile per wave 10 %
+// slower there, and no faster on fewer rows).
+extern "C" hipError_t surx_net(const __bf16 *const *wf, const float *const *bias, int mode, const float *params,
+                               const double *n0, void *out, int X, int B, hipStream_t s)
+{
+    const NetParams np = net_params(wf, bias);
+    const NetShape n = net_shape(X, B, net_rows(X, B, 192));
+    return n.rows == 192 ? launch_net<2>(np, mode, params, n0, out, X, n, s)
+                         : launch_net<1>(np, mode, params, n0, out, X, n, s);
+}
+
+// blocks of the training step's forward pass at most, one share of the loss each
+extern "C" int surx_net_train_blocks(int X, int B) { return (X + 32 - NET_HALO - 1) / (32 - NET_HALO) * B; }
+
+// The training step's forward pass: hidden outputs, features, the gradient at
+// the output and *blocks shares of the loss.
+extern "C" hipError_t surx_net_train(const __bf16 *const *wf, const float *const *bias, const float *params,
+                                     const float *target, float *const *y, __bf16 *feat, __bf16 *dz, double *loss,
+                                     int *blocks, int X, int B, hipStream_t s)
+{
+    NetTrain tr;
+    for (int l = 0; l < 5; ++l) tr.y[l] = y[l];
+    tr.feat = feat;
+    tr.target = target;
+    tr.dz = dz;
+    tr.loss = loss;
+    tr.B = B;
+    // one channel tile per wave throughout: with two (and 192 rows) the step of
+    // 32 samples x 2048 cells took 164 us, with 128 rows and one 154
+    const NetShape n = net_shape(X, B, net_rows(X, B, 128));
+    *blocks = (int)n.grid;
+    hipLaunchKernelGGL(k_net_train, dim3(n.grid), dim3(NET_THREADS), n.lds, s, net_params(wf, bias), params, tr, X,
+                       n.tiles, n.T, n.rows);
+    return hipGetLastError();
 }

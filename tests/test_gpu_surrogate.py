@@ -379,3 +379,30 @@ def test_forward_into_an_odd_offset(sur, torch):
     out = flat[1:1 + B * SO.N_OUT * X].view(B, SO.N_OUT, X)
     assert torch.equal(net.forward(p, out), ref)
     assert torch.isnan(flat[:1]).all() and torch.isnan(flat[1 + B * SO.N_OUT * X:]).all()
+
+
+@pytest.mark.parametrize("B,X", [(2, 64), (4, 320), (8, 704), (16, 64), (32, 1216), (4, 4096)])
+def test_train_step_on_every_tiling(sur, torch, B, X):
+    """The training step's rows per block follow the batch and the length.  Its
+    loss is the mean of the samples' own and its gradients the mean of theirs:
+    with a power of two samples the gradients at the output scale exactly, so
+    only FP32 sums of at most a few hundred partials differ (6e-8 times the
+    root of their number, below 1e-5)."""
+    _say("case: train step tilings B=%d X=%d" % (B, X))
+    W, b = presets.surrogate_test_weights(29)
+    p = torch.tensor(_params(B, 37), dtype=torch.float32, device="cuda:0")
+    u = np.linspace(0.5 / X, 1 - 0.5 / X, X)
+    t = torch.tensor(np.stack([_target39(u, k) for k in range(B)]), dtype=torch.float32, device="cuda:0")
+    net = sur.Surrogate(B, X, device="cuda:0")
+    net.set_weights(W, b)
+    loss = net.train_step(p, t, 1e-3)
+    gw, gb = net.grads()
+    losses, sw, sb = [], [np.zeros_like(x, np.float64) for x in gw], [np.zeros_like(x, np.float64) for x in gb]
+    for k in range(B):
+        net.set_weights(W, b)
+        losses.append(net.train_step(p[k:k + 1], t[k:k + 1], 1e-3))
+        for s, g in zip(sw + sb, sum(net.grads(), [])):
+            s += g.astype(np.float64) / B
+    assert abs(loss - np.mean(losses)) <= 1e-12 * loss
+    for s, g in zip(sw + sb, gw + gb):
+        assert _rel(g, s) <= 1e-5
