@@ -306,14 +306,24 @@ struct pic_handle {
 
 namespace {
 
+// The particle kernel's grid when the caller names none.  A CU holds four of
+// its blocks (123 registers), so 1024 blocks are one round: best while a
+// block's share stays short (a block's run works off its rare items at its
+// end, and with every block in one round nothing else runs meanwhile).  Above
+// 20 chunks a block, eight chunks a block in several rounds; up to 1408 chunks
+// in all, one chunk a block.  Measured, us per step at 1024 / 1536 / 2048 /
+// 4096 / 8192 blocks: 3280 cells, 1.3k chunks 24.2 / 23.0 / 23.0 / 23.5 / 28;
+// 2048 cells, 1.5k chunks 24.1 / 26.2 / 26.2 / 26.5 / 31; the paper's diode,
+// 16k chunks 57 / 65 / 59 / 64 / 84; eleven diodes, 30k chunks 118 / 123 / 115
+// / 103 / 113; the sweep, 42k chunks 159 / 158 / 154 / 148 / 150; the large
+// diode, 63k chunks 219 / 213 / 212 / 185 / 184.
 int grid_for(const pic_handle *h)
 {
     int64_t chunks = 0;
-    for (int d = 0; d < h->nd; ++d)
-        for (int s = 0; s < NSP; ++s) chunks += (h->der[d].capacity[s] + 256 * h->ppt - 1) / (256 * h->ppt);
-    int64_t g = std::min<int64_t>(chunks, 8192);
-    g = std::max<int64_t>(8, (g + 7) / 8 * 8);
-    return (int)g;
+    for (int d = 0; d < h->nd; ++d) chunks += 2 * ((h->cfg[d].n_load + 256 * h->ppt - 1) / (256 * h->ppt));
+    if (chunks <= 1408) return 1536;
+    if (chunks <= 20 * 1024) return 1024;
+    return (int)std::min<int64_t>(8192, (chunks / 8 + 1023) / 1024 * 1024);
 }
 
 // parity: buffer current before the re-sort; the re-sort flips it
@@ -1206,7 +1216,7 @@ int pic_autotune(pic_handle *h, int64_t trial_steps, int *ppt, int *grid, int *s
         // powers of two and the points half way between them (the best grid
         // is not monotone in the chunks per block: the paper's eleven-flux
         // batch ran 71.9 us per step at 3072 blocks, 73.0 at 4096)
-        std::vector<int> grids = {2048, 3072, 4096, 6144, 8192, 12288, 16384};
+        std::vector<int> grids = {1024, 2048, 3072, 4096, 6144, 8192, 12288, 16384};
         bool near = false;
         for (int g : grids) near = near || std::abs(g - g8) * 10 < g;
         if (!near) grids.push_back(g8);

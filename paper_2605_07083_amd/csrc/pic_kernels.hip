@@ -13,9 +13,9 @@
 //                     and the field, tallies and snapshots (k_field_tiles on
 //                     grids above 2049 nodes).
 // Particles are processed in chunks of 256*PPT slots; the chunk list spans all
-// (diode, species) segments.  Each block of the particle kernel takes an equal
-// share of it, in an order that puts every segment's unsorted tail (the
-// particles born since the last re-sort) before the sorted bodies.
+// (diode, species) segments.  The segments' unsorted tails (the particles born
+// since the last re-sort) are dealt to the particle kernel's blocks chunk by
+// chunk, and every block takes a contiguous range of the sorted bodies.
 #include "pic_internal.h"
 
 namespace pic {
@@ -323,9 +323,9 @@ __device__ __forceinline__ int find_seg(const int *seg_end, int nseg, int c)
 // last re-sort left (n_new), ordered by bin; its tail is the rest, the
 // particles born since (plus the chunk that straddles n_new).  Newborns of
 // ionisation lie anywhere in the gap, so a tail run gathers and deposits
-// mostly outside its window and costs a block several times a body run: at
-// the head of the order such blocks start first and end inside the kernel,
-// not after it.  tail_end and body_end are inclusive prefix sums of the
+// mostly outside its window and costs a block several times a body run: the
+// first blocks take such runs, before their body chunks, and end inside the
+// kernel, not after it.  tail_end and body_end are inclusive prefix sums of the
 // segments' tail and body chunk counts.
 struct TailFirstMap {
     int nseg;
@@ -689,6 +689,11 @@ __device__ __forceinline__ void flush_run(int j, unsigned long long P, int w0, i
     }
 }
 
+// A tail chunk's cost in body chunks, for the blocks' shares: its run's set-up
+// (a chain of memory round trips, about 5.5 us where a chunk streams in 1.9)
+// and its deposits outside the window.
+constexpr int TAIL_COST = 3;
+
 #ifndef PIC_PARTICLE_MIN_WAVES
 #define PIC_PARTICLE_MIN_WAVES 1
 #endif
@@ -713,26 +718,48 @@ __global__ __launch_bounds__(NT, PIC_PARTICLE_MIN_WAVES) void k_particles(const 
     build_tail_first_map(S, nd, CHUNK, tail_end, body_end, seg_n, cm);
     const int tid = threadIdx.x;
     const int w = tid >> 6, lane = tid & 63;
-    const int per_block = (cm.total + gridDim.x - 1) / gridDim.x;
-    const int v_begin = blockIdx.x * per_block;
-    const int v_end = min(cm.total, v_begin + per_block);
+    // The block's share: tail chunks one by one (tail chunk b, b + grid, ...),
+    // then a contiguous range of the bodies' chunks, shorter where there was a
+    // tail.  A batch has a tail per diode and species: in equal shares of one
+    // order the first block took a run of its own for each of its chunks, one
+    // after another, and ended last (eleven diodes at 1024 blocks: 139 us,
+    // dealt out 59; at 3072 blocks 61 and 59).
+    const int G = (int)gridDim.x, bid = (int)blockIdx.x;
+    const int nbody = cm.total - cm.ntail;
+    int tv = bid, u, u_end;
+    if (cm.total <= G) {
+        // a chunk per block at most
+        u = bid < cm.ntail ? nbody : bid - cm.ntail;
+        u_end = min(nbody, u + 1);
+    } else {
+        const int with_tail = min(cm.ntail, G);
+        int cap = (nbody + TAIL_COST * cm.ntail + G - 1) / G, cap_tail = max(0, cap - TAIL_COST);
+        if (__builtin_expect(with_tail == G || cap_tail == 0, 0)) {
+            asm volatile("");            // keeps these divisions off the common path
+            if (with_tail == G) cap = cap_tail = (nbody + G - 1) / G;
+            else cap = (nbody + G - with_tail - 1) / (G - with_tail);
+        }
+        u = bid < with_tail ? bid * cap_tail : with_tail * cap_tail + (bid - with_tail) * cap;
+        u_end = min(nbody, u + (bid < with_tail ? cap_tail : cap));
+    }
 
-    for (int v = v_begin; v < v_end;) {
+    while (true) {
         // the run: chunks [p0, p0 + nrun) of one segment's tail or body
-        const bool tail = v < cm.ntail;
-        int seg, p0, avail;
-        if (tail) {
-            seg = uni(find_seg(tail_end, cm.nseg, v));
+        int seg, p0, nrun;
+        if (tv < cm.ntail) {
+            seg = uni(find_seg(tail_end, cm.nseg, tv));
             const int tb = seg ? tail_end[seg - 1] : 0;
-            p0 = uni(body_end[seg] - (seg ? body_end[seg - 1] : 0) + v - tb);
-            avail = uni(tail_end[seg] - v);
-        } else {
-            const int u = v - cm.ntail;
+            p0 = uni(body_end[seg] - (seg ? body_end[seg - 1] : 0) + tv - tb);
+            nrun = 1;
+            tv += G;
+        } else if (u < u_end) {
             seg = uni(find_seg(body_end, cm.nseg, u));
             p0 = uni(u - (seg ? body_end[seg - 1] : 0));
-            avail = uni(body_end[seg] - u);
+            nrun = uni(min(min(u_end, body_end[seg]) - u, RUN_CHUNKS));
+            u += nrun;
+        } else {
+            break;
         }
-        const int nrun = uni(min(min(v_end - v, avail), RUN_CHUNKS));
         const int d = seg / NSP, s = seg - d * NSP;
         const Diode &dd = D[d];
         const GBuf b = gbuf(dd.buf[parity ^ uni(S[d].flip[s])][s]);
@@ -945,7 +972,6 @@ __global__ __launch_bounds__(NT, PIC_PARTICLE_MIN_WAVES) void k_particles(const 
             }
         }
         lds_barrier();
-        v += nrun;
     }
 }
 
