@@ -284,8 +284,8 @@ int pic_set_counters(pic_handle *h, int diode, int64_t step, uint32_t next_id);
 int pic_refield(pic_handle *h);
 
 /* Per-kernel timing: run nsteps steps on the current schedule -- with graph
- * replay, each run up to the next re-sort boundary is one replayed graph, as
- * in pic_step -- with HIP events around launches of the particle kernel on
+ * replay, each run up to the next re-sort boundary is one replayed graph
+ * (pic_step replays whole re-sort periods only) -- with HIP events around launches of the particle kernel on
  * the bound stream (with graph replay: the particle kernels of up to 8 steps
  * spread evenly over each replayed run, at most 4096 in all; on the plain
  * stream, where each pair of timestamps stalls the launches around it, at
