@@ -306,22 +306,33 @@ struct pic_handle {
 
 namespace {
 
-// The particle kernel's grid when the caller names none.  A CU holds four of
-// its blocks (123 registers), so 1024 blocks are one round: best while a
-// block's share stays short (a block's run works off its rare items at its
-// end, and with every block in one round nothing else runs meanwhile).  Above
-// 20 chunks a block, eight chunks a block in several rounds; up to 1408 chunks
-// in all, one chunk a block.  Measured, us per step at 1024 / 1536 / 2048 /
-// 4096 / 8192 blocks: 3280 cells, 1.3k chunks 24.2 / 23.0 / 23.0 / 23.5 / 28;
-// 2048 cells, 1.5k chunks 24.1 / 26.2 / 26.2 / 26.5 / 31; the paper's diode,
-// 16k chunks 57 / 65 / 59 / 64 / 84; eleven diodes, 30k chunks 118 / 123 / 115
-// / 103 / 113; the sweep, 42k chunks 159 / 158 / 154 / 148 / 150; the large
-// diode, 63k chunks 219 / 213 / 212 / 185 / 184.
+// The schedule when the caller names none.  A CU holds four of the particle
+// kernel's blocks (three with four particles per thread), so 1024 (768) blocks
+// are one round.  Particles per thread: as few as let every block have one
+// chunk in one round; two where none does.  Measured, us per step with one /
+// two / four (2048 cells, best grid): 0.20M particles 18.0 / 18.4 / 20.2, 0.39M
+// 20.6 / 19.7 / 21.3, 0.69M 22.7 / 22.9 / 22.4, 0.79M 23.5 / 23.7 / 22.7,
+// 0.99M 24.6 / 23.0 / 25.8.
+int ppt_for(const pic_handle *h)
+{
+    int64_t total = 0;
+    for (int d = 0; d < h->nd; ++d) total += 2 * h->cfg[d].n_load;
+    if (total <= 1024 * 256) return 1;
+    return total > 1024 * 512 && total <= 800 * 1024 ? 4 : 2;
+}
+
+// Grid: one round of blocks is best while a block's share stays short (a
+// block's run works off its rare items at its end, and with every block in one
+// round nothing else runs meanwhile).  Above 20 chunks a block, eight chunks a
+// block in several rounds.  Measured, us per step at 1024 / 1536 / 2048 / 4096
+// / 8192 blocks: 2048 cells, 1.5k chunks 24.1 / 26.2 / 26.2 / 26.5 / 31; the
+// paper's diode, 16k chunks 57 / 65 / 59 / 64 / 84; eleven diodes, 30k chunks
+// 118 / 123 / 115 / 103 / 113; the sweep, 42k chunks 159 / 158 / 154 / 148 /
+// 150 (141 at 6144); the large diode, 63k chunks 219 / 213 / 212 / 185 / 184.
 int grid_for(const pic_handle *h)
 {
     int64_t chunks = 0;
     for (int d = 0; d < h->nd; ++d) chunks += 2 * ((h->cfg[d].n_load + 256 * h->ppt - 1) / (256 * h->ppt));
-    if (chunks <= 1408) return 1536;
     if (chunks <= 20 * 1024) return 1024;
     return (int)std::min<int64_t>(8192, (chunks / 8 + 1023) / 1024 * 1024);
 }
@@ -651,6 +662,7 @@ static int init_impl(const pic_config *cfgs, int n_diodes, void *dev_workspace, 
         h->max_nodes = std::max(h->max_nodes, cfgs[d].N + 1);
     }
     h->dS = h->hD[0].st;
+    h->ppt = ppt_for(h);
     h->grid = grid_for(h);
 
     auto cleanup = [&](int code) { delete h; return code; };

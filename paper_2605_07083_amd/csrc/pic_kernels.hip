@@ -16,6 +16,8 @@
 // (diode, species) segments.  The segments' unsorted tails (the particles born
 // since the last re-sort) are dealt to the particle kernel's blocks chunk by
 // chunk, and every block takes a contiguous range of the sorted bodies.
+#include <cstddef>
+
 #include "pic_internal.h"
 
 namespace pic {
@@ -251,6 +253,25 @@ __device__ __forceinline__ void run_extent(int key, int &start, int &len)
 // buffer pointers, parameters) lives in scalar registers.
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// Inclusive wave scan with DPP moves (ALU-latency lane exchanges, where a
+// shuffle goes through the LDS crossbar and waits for it): shifts by 1, 2, 4
+// and 8 lanes within each row of 16 (zero entering from the row's start),
+// then the row totals broadcast from lane 15 into rows 1 and 3 and from lane
+// 31 into rows 2 and 3.  Every lane of the wave must be active.
+constexpr int DPP_ROW_SHR1 = 0x111, DPP_ROW_SHR2 = 0x112, DPP_ROW_SHR4 = 0x114, DPP_ROW_SHR8 = 0x118;
+constexpr int DPP_ROW_BCAST15 = 0x142, DPP_ROW_BCAST31 = 0x143;
+
+__device__ __forceinline__ int wave_incl_scan_i32(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR1, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR2, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR4, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_SHR8, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_BCAST15, 0xa, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, DPP_ROW_BCAST31, 0xc, 0xf, true);
+    return x;
+}
+
 struct ChunkMap {
     int nseg;
     int total;
@@ -293,14 +314,9 @@ __device__ void build_chunk_map(const Diode *__restrict__ D, const DiodeState *_
                 c = kept ? 0 : (n + chunk - 1) / chunk;
                 if (seg_n) seg_n[sidx] = n;
             }
-            // inclusive wave scan
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                int t = __shfl_up(c, o, 64);
-                if ((int)threadIdx.x >= o) c += t;
-            }
+            c = wave_incl_scan_i32(c);
             if (sidx < nseg) seg_end[sidx] = c + carry;
-            carry += __shfl(c, 63, 64);
+            carry += __builtin_amdgcn_readlane(c, 63);
         }
     }
     __syncthreads();
@@ -308,14 +324,17 @@ __device__ void build_chunk_map(const Diode *__restrict__ D, const DiodeState *_
     cm.total = uni(seg_end[nseg - 1]);
 }
 
+// The segment of chunk c: the number of segments that end at or before it,
+// every lane comparing one (a binary search would wait for LDS at each step).
+// Every lane of the wave must be active; c is uniform.
 __device__ __forceinline__ int find_seg(const int *seg_end, int nseg, int c)
 {
-    int lo = 0, hi = nseg - 1;
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (seg_end[mid] > c) hi = mid; else lo = mid + 1;
+    int seg = 0;
+    for (int b0 = 0; b0 < nseg; b0 += 64) {
+        const int i = b0 + (int)(threadIdx.x & 63);
+        seg += __popcll(__ballot(i < nseg && seg_end[i] <= c));
     }
-    return lo;
+    return seg;
 }
 
 // Chunk order of the particle kernel: the tails of all segments first, then
@@ -326,7 +345,8 @@ __device__ __forceinline__ int find_seg(const int *seg_end, int nseg, int c)
 // mostly outside its window and costs a block several times a body run: the
 // first blocks take such runs, before their body chunks, and end inside the
 // kernel, not after it.  tail_end and body_end are inclusive prefix sums of the
-// segments' tail and body chunk counts.
+// segments' tail and body chunk counts; seg_n holds a segment's slot count with
+// its buffer flip in the top bit (a capacity is below 2^31).
 struct TailFirstMap {
     int nseg;
     int ntail;   // tail chunks of all segments
@@ -348,19 +368,16 @@ __device__ void build_tail_first_map(const DiodeState *__restrict__ S, int nd, i
                 const int ns = min(max(st.n_new[sidx % NSP], 0), n);
                 cb = ns / chunk;
                 ct = (n + chunk - 1) / chunk - cb;
-                seg_n[sidx] = n;
+                seg_n[sidx] = (int)((uint32_t)n | (uint32_t)st.flip[sidx % NSP] << 31);
             }
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(ct, o, 64), u = __shfl_up(cb, o, 64);
-                if ((int)threadIdx.x >= o) { ct += t; cb += u; }
-            }
+            ct = wave_incl_scan_i32(ct);
+            cb = wave_incl_scan_i32(cb);
             if (sidx < nseg) {
                 tail_end[sidx] = ct + carry_t;
                 body_end[sidx] = cb + carry_b;
             }
-            carry_t += __shfl(ct, 63, 64);
-            carry_b += __shfl(cb, 63, 64);
+            carry_t += __builtin_amdgcn_readlane(ct, 63);
+            carry_b += __builtin_amdgcn_readlane(cb, 63);
         }
     }
     __syncthreads();
@@ -574,23 +591,30 @@ __device__ __forceinline__ void process_rare(const Diode &dd, const int *rare_n,
     }
 }
 
-// Add a block-run tally to this block's accumulator copy (device atomics).
-__device__ __forceinline__ void flush_tally(const Diode &dd, const RareTally &t)
+// Add a run's tally to the block's accumulator copy (device atomics) and clear
+// it: a lane per field (one thread going through them, each a wait for LDS,
+// took 2200 cycles of every run).  Called by the first wave's lanes.
+constexpr int RT_COUNTS = (int)(offsetof(RareTally, abs_energy) / sizeof(unsigned));
+static_assert(RT_COUNTS == 2 + NCH + 2 * NSP + 1 && sizeof(RareTally) == offsetof(RareTally, abs_energy) + 2 * NSP * sizeof(double),
+              "counts, then energies");
+__device__ __forceinline__ void flush_tally(const Diode &dd, RareTally *t, int lane)
 {
-    RareTally &a = dd.tacc[blockIdx.x % TALLY_COPIES].t;
-    for (int ion = 0; ion < 2; ++ion)
-        if (t.cand[ion]) atomicAdd(&a.cand[ion], t.cand[ion]);
-#pragma unroll
-    for (int k = 0; k < NCH; ++k)
-        if (t.coll[k]) atomicAdd(&a.coll[k], t.coll[k]);
-#pragma unroll
-    for (int sp = 0; sp < NSP; ++sp)
-        for (int w = 0; w < 2; ++w)
-            if (t.abs_count[sp][w]) {
-                atomicAdd(&a.abs_count[sp][w], t.abs_count[sp][w]);
-                atomicAdd(&a.abs_energy[sp][w], t.abs_energy[sp][w]);
-            }
-    if (t.ion_lost) atomicAdd(&a.ion_lost, t.ion_lost);
+    RareTally *a = &dd.tacc[blockIdx.x % TALLY_COPIES].t;
+    if (lane < RT_COUNTS) {
+        unsigned *p = reinterpret_cast<unsigned *>(t) + lane;
+        const unsigned v = *p;
+        if (v) {
+            __hip_atomic_fetch_add(glb(reinterpret_cast<unsigned *>(a) + lane), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *p = 0u;
+        }
+    } else if (lane >= 32 && lane < 32 + 2 * NSP) {
+        double *p = &t->abs_energy[0][0] + (lane - 32);
+        const double v = *p;
+        if (v != 0.0) {
+            atomicAdd(&a->abs_energy[0][0] + (lane - 32), v);
+            *p = 0.0;
+        }
+    }
 }
 
 // Fold the accumulator copies (one per lane of the first wave, read by
@@ -694,11 +718,11 @@ __device__ __forceinline__ void flush_run(int j, unsigned long long P, int w0, i
 // and its deposits outside the window.
 constexpr int TAIL_COST = 3;
 
-#ifndef PIC_PARTICLE_MIN_WAVES
-#define PIC_PARTICLE_MIN_WAVES 1
-#endif
+// Waves per SIMD asked for: four (128 registers) with one or two particles per
+// thread.  With five the sweep's step took 143 us instead of 147, but the
+// paper's diode 60 instead of 57; six spill (every workload 10 to 20 % slower).
 template <int PPT>
-__global__ __launch_bounds__(NT, PIC_PARTICLE_MIN_WAVES) void k_particles(const Diode *__restrict__ D, const DiodeState *__restrict__ S,
+__global__ __launch_bounds__(NT, PPT <= 2 ? 4 : 1) void k_particles(const Diode *__restrict__ D, const DiodeState *__restrict__ S,
                                                   int nd, int mode, int parity)
 {
     constexpr int CHUNK = NT * PPT;
@@ -713,10 +737,10 @@ __global__ __launch_bounds__(NT, PIC_PARTICLE_MIN_WAVES) void k_particles(const 
     __shared__ int q_n[NW];
     __shared__ RareTally rt;
 
+    const int tid = threadIdx.x;
     if (threadIdx.x == 0) rare_tally_zero(&rt);
     TailFirstMap cm;
     build_tail_first_map(S, nd, CHUNK, tail_end, body_end, seg_n, cm);
-    const int tid = threadIdx.x;
     const int w = tid >> 6, lane = tid & 63;
     // The block's share: tail chunks one by one (tail chunk b, b + grid, ...),
     // then a contiguous range of the bodies' chunks, shorter where there was a
@@ -729,6 +753,7 @@ __global__ __launch_bounds__(NT, PIC_PARTICLE_MIN_WAVES) void k_particles(const 
     int tv = bid, u, u_end;
     if (cm.total <= G) {
         // a chunk per block at most
+        if (bid >= cm.total) return;
         u = bid < cm.ntail ? nbody : bid - cm.ntail;
         u_end = min(nbody, u + 1);
     } else {
@@ -762,10 +787,11 @@ __global__ __launch_bounds__(NT, PIC_PARTICLE_MIN_WAVES) void k_particles(const 
         }
         const int d = seg / NSP, s = seg - d * NSP;
         const Diode &dd = D[d];
-        const GBuf b = gbuf(dd.buf[parity ^ uni(S[d].flip[s])][s]);
+        const uint32_t nf = (uint32_t)uni(seg_n[seg]);
+        const GBuf b = gbuf(dd.buf[parity ^ (int)(nf >> 31)][s]);
         const int N = dd.N;
         const double invdz = dd.invdz;
-        const int n = uni(seg_n[seg]);
+        const int n = (int)(nf & 0x7FFFFFFFu);
         const int slot0 = p0 * CHUNK;
 
         const uint32_t step = (uint32_t)uni((int)S[d].step);
@@ -966,10 +992,7 @@ __global__ __launch_bounds__(NT, PIC_PARTICLE_MIN_WAVES) void k_particles(const 
                 else rare_absorbed(dd, s, b, i, (int)kind - 1, rq_v[wq][k], &rt);
             }
             lds_barrier();
-            if (tid == 0) {
-                flush_tally(dd, rt);
-                rare_tally_zero(&rt);
-            }
+            if (w == 0) flush_tally(dd, &rt, lane);
         }
         lds_barrier();
     }
@@ -1603,14 +1626,7 @@ __device__ void write_particle(const GBuf &b, int i, double z, float vx, float v
     put_cold(&b.cold[i], vx, vy, id);
 }
 
-// Inclusive wave scans with DPP moves (ALU-latency lane exchanges, where a
-// shuffle goes through the LDS crossbar and waits for it): shifts by 1, 2, 4
-// and 8 lanes within each row of 16 (zero entering from the row's start),
-// then the row totals broadcast from lane 15 into rows 1 and 3 and from lane
-// 31 into rows 2 and 3.  Every lane of the wave must be active.
-constexpr int DPP_ROW_SHR1 = 0x111, DPP_ROW_SHR2 = 0x112, DPP_ROW_SHR4 = 0x114, DPP_ROW_SHR8 = 0x118;
-constexpr int DPP_ROW_BCAST15 = 0x142, DPP_ROW_BCAST31 = 0x143;
-
+// The 64- and 128-bit forms of wave_incl_scan_i32.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v)
 {
