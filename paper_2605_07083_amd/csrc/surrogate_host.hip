@@ -5,6 +5,7 @@
 // Adam with re-quantisation).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -59,6 +60,7 @@ constexpr int COUTP[SUR_LAYERS] = {64, 64, 64, 64, 64, 48};
 constexpr float B1 = 0.9f, B2 = 0.999f, EPS = 1e-8f;
 
 int pad32(int k) { return (k + 31) / 32 * 32; }
+size_t align_up(size_t n) { return (n + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Layer {
     int cin, cout, coutp, kp, kpb;
@@ -127,12 +129,39 @@ void layout(sur_net &n, Bump &bp)
     n.loss = bp.take<double>(1);
     n.param_bytes = bp.off;
     n.feat = bp.take<__bf16>(P * SUR_IN);
-    for (int l = 0; l < SUR_LAYERS - 1; ++l) n.y[l] = bp.take<float>(P * SUR_HIDDEN);
     for (int k = 0; k < 2; ++k) n.dz[k] = bp.take<__bf16>(P * SUR_HIDDEN);
+    // One region for the hidden outputs and the partial gradients.  The
+    // backward pass goes from the last layer to the first and layer l reads
+    // y[l-1] only, so the partials are laid out in that order from the
+    // region's start and the outputs, last layer first, `fresh` bytes in: the
+    // partials of layer l may end where y[l-1] begins.  Grids of whole
+    // 256-position slices need 500 bytes per position before y[4], short
+    // samples more; the region is never below 832 bytes per position and the
+    // largest layer's partials, a size that callers may have planned with.
     const size_t parts = (size_t)surx_wgrad_parts(n.X, n.bmax);
-    for (int l = 0; l < SUR_LAYERS; ++l) {
-        n.part[l] = bp.take<float>(parts * n.L[l].coutp * n.L[l].kp);
-        n.pbias[l] = bp.take<float>(parts * n.L[l].coutp);
+    const size_t ybytes = align_up(P * SUR_HIDDEN * sizeof(float));
+    size_t wbytes[SUR_LAYERS], bbytes[SUR_LAYERS], end = 0, fresh = 0, largest = 0;
+    for (int l = SUR_LAYERS - 1; l >= 0; --l) {
+        wbytes[l] = align_up(parts * n.L[l].coutp * n.L[l].kp * sizeof(float));
+        bbytes[l] = align_up(parts * n.L[l].coutp * sizeof(float));
+        end += wbytes[l] + bbytes[l];
+        largest = std::max(largest, wbytes[l] + bbytes[l]);
+        const size_t dead = (size_t)(SUR_LAYERS - 1 - std::max(l, 1)) * ybytes;   // y[4] .. y[l]
+        if (l > 0 && end > dead) fresh = std::max(fresh, end - dead);
+    }
+    const size_t region = std::max({fresh + (SUR_LAYERS - 1) * ybytes, end,
+                                    align_up(P * 832) + largest + (SUR_LAYERS - 1) * ybytes});
+    fresh = region - (SUR_LAYERS - 1) * ybytes;
+    char *r = bp.take<char>(region);
+    if (r) {
+        size_t off = 0;
+        for (int l = SUR_LAYERS - 1; l >= 0; --l) {
+            n.part[l] = reinterpret_cast<float *>(r + off);
+            n.pbias[l] = reinterpret_cast<float *>(r + off + wbytes[l]);
+            off += wbytes[l] + bbytes[l];
+        }
+        for (int l = 0; l < SUR_LAYERS - 1; ++l)
+            n.y[l] = reinterpret_cast<float *>(r + fresh + (SUR_LAYERS - 2 - l) * ybytes);
     }
     n.loss_parts = bp.take<double>((size_t)surx_net_train_blocks(n.X, n.bmax));
 }
