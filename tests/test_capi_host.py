@@ -73,6 +73,23 @@ def test_derived_match_oracle(O, name):
     assert all(c % 2048 == 0 and c >= p["n_load"] for c in a["capacity"])
 
 
+@pytest.mark.parametrize("seed", range(40))
+def test_null_collision_bound_is_the_full_scan_s(O, seed):
+    """The searched bound is the same double as the oracle's scan of every grid
+    speed: peaks inside and outside the range, single channels, channels that
+    dwarf the others, cross sections of either sign, and values that are not
+    finite."""
+    rng = np.random.default_rng(0xB0D + seed)
+    p = dict(getattr(presets, ["tiny", "large"][seed % 2])())
+    for k in ("sig_el", "sig_x0", "lotz_a", "sig_cx", "sig_iel"):
+        p[k] *= rng.choice([0.0, 1.0, 10.0 ** rng.uniform(-3, 3), -0.5], p=[0.1, 0.2, 0.6, 0.1])
+    p["V"] = float(rng.choice([0.0, 10.0 ** rng.uniform(-1, 5), np.inf, np.nan], p=[0.1, 0.8, 0.05, 0.05]))
+    p["Te0"], p["Tc"] = float(rng.choice([0.0, 0.2, 30.0])), float(rng.choice([0.0, 0.2]))
+    p["channels"] = int(rng.integers(0, 32))
+    a, b = pic.pic_derive(p)["numax"], O.derive(p)["numax"]
+    assert np.array_equal(a, b, equal_nan=True)
+
+
 def test_sweep_derived_and_workspace():
     cfgs = presets.sweep()
     assert len(cfgs) == 32
