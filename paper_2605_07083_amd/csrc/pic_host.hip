@@ -32,7 +32,7 @@ extern "C" hipError_t picx_launch_sources_field(const Diode *D, DiodeState *S, i
 extern "C" hipError_t picx_prepare(void);
 extern "C" hipError_t picx_launch_phase_hist(const Diode *D, const DiodeState *S, int d, int s, int parity, int nz,
                                              int nv, double sz, double vmin, double sv, unsigned long long *out,
-                                             int blocks, hipStream_t st);
+                                             int64_t capacity, hipStream_t st);
 extern "C" int picx_sources_field_kernels(int max_nodes, int mode);
 extern "C" hipError_t picx_launch_profile_load(const Diode *D, const double *dens, int rows, int nd, int max_cells,
                                                hipStream_t s);
@@ -997,10 +997,9 @@ int pic_phase_space(pic_handle *h, int diode, int species, int nz, int nv, doubl
         return fail(PIC_EINVAL, "dev_out must be device memory on the handle's GPU");
     const double sz = (double)nz / h->cfg[diode].L;
     const double sv = (double)nv / (vmax - vmin);
-    const int64_t cap = h->der[diode].capacity[species];
-    const int blocks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (cap + 4095) / 4096));
     HIP_TRY(picx_launch_phase_hist(h->dD, h->dS, diode, species, h->parity, nz, nv, sz, vmin, sv,
-                                   reinterpret_cast<unsigned long long *>(dev_out), blocks, h->stream));
+                                   reinterpret_cast<unsigned long long *>(dev_out), h->der[diode].capacity[species],
+                                   h->stream));
     return PIC_OK;
 }
 

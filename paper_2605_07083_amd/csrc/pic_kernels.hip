@@ -1226,29 +1226,59 @@ __global__ __launch_bounds__(256) void k_profile_clear(const Diode *__restrict__
 // range (a narrow range of cells once sorted) in LDS and adds its nonzero bins
 // to the caller's uint64 counts.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_phase_hist(const Diode *__restrict__ D, const DiodeState *__restrict__ S,
-                                                    int d, int s, int parity, int nz, int nv, double sz, double vmin,
-                                                    double sv, unsigned long long *__restrict__ out)
+//
+// Bound by the 12 bytes read per particle.  Each thread has PH_AHEAD particles
+// in flight, the next ones requested before the counted ones go to LDS.  One
+// large block per CU at most, and never less than one round of particles per
+// block: the counts' clearing and flush is what a block costs (1024 blocks of
+// 256 threads took 13.5 us over 2547 particles and 17.0 us over 4.1 million;
+// this takes 4.6 us and 9.6 us, eight particles ahead 10.1 us, 256 threads
+// with eight 13.5 us).
+constexpr int PH_THREADS = 1024, PH_AHEAD = 4, PH_BLOCKS = 256;
+__global__ __launch_bounds__(PH_THREADS) void k_phase_hist(const Diode *__restrict__ D,
+                                                           const DiodeState *__restrict__ S, int d, int s, int parity,
+                                                           int nz, int nv, double sz, double vmin, double sv,
+                                                           unsigned long long *__restrict__ out)
 {
     extern __shared__ uint32_t ph_hist[];
     const int W = nv + 2, nb = nz * W, tid = threadIdx.x;
-    for (int i = tid; i < nb; i += 256) ph_hist[i] = 0u;
-    const Diode &dd = D[d];
-    const GBuf b = gbuf(dd.buf[parity ^ S[d].flip[s]][s]);
+    const SpeciesBuf b0 = D[d].buf[0][s], b1 = D[d].buf[1][s];
     const int n = S[d].n[s];
-    const int per = (n + (int)gridDim.x - 1) / (int)gridDim.x;
+    const bool second = (parity ^ S[d].flip[s]) != 0;
+    const GBuf b = gbuf(second ? b1 : b0);
+    const int per = max((n + (int)gridDim.x - 1) / (int)gridDim.x, PH_THREADS * PH_AHEAD);
     const int i0 = (int)blockIdx.x * per, i1 = min(n, i0 + per);
+    if (i0 >= i1) return;
+    double z[PH_AHEAD];
+    float v[PH_AHEAD];
+    auto fetch = [&](int base) {
+#pragma unroll
+        for (int k = 0; k < PH_AHEAD; ++k) {
+            const int i = min(base + k * PH_THREADS + tid, i1 - 1);
+            z[k] = b.z[i];
+            v[k] = b.vz[i];
+        }
+    };
+    fetch(i0);
+    for (int i = tid; i < nb; i += PH_THREADS) ph_hist[i] = 0u;
     __syncthreads();
-    for (int i = i0 + tid; i < i1; i += 256) {
-        const double z = b.z[i];
-        if (!(z >= 0.0)) continue;                     // hole
-        const int iz = min(nz - 1, (int)(z * sz));
-        const double x = ((double)b.vz[i] - vmin) * sv;
-        const int iv = x >= (double)nv ? nv + 1 : (x >= 0.0 ? 1 + (int)x : 0);
-        atomicAdd(&ph_hist[iz * W + iv], 1u);
+    for (int base = i0; base < i1; base += PH_AHEAD * PH_THREADS) {
+        int bin[PH_AHEAD];
+#pragma unroll
+        for (int k = 0; k < PH_AHEAD; ++k) {
+            const int iz = min(nz - 1, (int)(z[k] * sz));
+            const double x = ((double)v[k] - vmin) * sv;
+            const int iv = x >= (double)nv ? nv + 1 : (x >= 0.0 ? 1 + (int)x : 0);
+            // a hole or a slot past the end
+            bin[k] = z[k] >= 0.0 && base + k * PH_THREADS + tid < i1 ? iz * W + iv : -1;
+        }
+        if (base + PH_AHEAD * PH_THREADS < i1) fetch(base + PH_AHEAD * PH_THREADS);
+#pragma unroll
+        for (int k = 0; k < PH_AHEAD; ++k)
+            if (bin[k] >= 0) atomicAdd(&ph_hist[bin[k]], 1u);
     }
     __syncthreads();
-    for (int i = tid; i < nb; i += 256) {
+    for (int i = tid; i < nb; i += PH_THREADS) {
         const uint32_t c = ph_hist[i];
         if (c) atomicAdd(&out[i], (unsigned long long)c);
     }
@@ -1256,10 +1286,12 @@ __global__ __launch_bounds__(256) void k_phase_hist(const Diode *__restrict__ D,
 
 extern "C" hipError_t picx_launch_phase_hist(const Diode *D, const DiodeState *S, int d, int s, int parity, int nz,
                                              int nv, double sz, double vmin, double sv, unsigned long long *out,
-                                             int blocks, hipStream_t st)
+                                             int64_t capacity, hipStream_t st)
 {
     const size_t lds = (size_t)nz * (nv + 2) * sizeof(uint32_t);
-    hipLaunchKernelGGL(k_phase_hist, dim3(blocks), dim3(256), lds, st, D, S, d, s, parity, nz, nv, sz, vmin, sv,
+    const int64_t rounds = (capacity + PH_THREADS * PH_AHEAD - 1) / (PH_THREADS * PH_AHEAD);
+    const int blocks = (int)std::min<int64_t>(PH_BLOCKS, std::max<int64_t>(1, rounds));
+    hipLaunchKernelGGL(k_phase_hist, dim3(blocks), dim3(PH_THREADS), lds, st, D, S, d, s, parity, nz, nv, sz, vmin, sv,
                        out);
     return hipGetLastError();
 }

@@ -405,3 +405,19 @@ def test_block_shares_cover_every_chunk(pic, ppt, grid):
             pa, pb = a.particles(d, sp), b.particles(d, sp)
             for k in pa:
                 assert np.array_equal(pa[k], pb[k])
+
+
+@pytest.mark.parametrize("n_load", [1, 4095, 4096, 4097, 8193, 40961])
+def test_phase_space_rounds(pic, O, n_load):
+    """A block of the phase-space kernel counts whole rounds of 4096 slots:
+    loads around one round, two, and eleven, freshly loaded and with holes."""
+    cfg = presets.scaled(presets.tiny(), n_load=n_load)
+    h = pic.Handle(cfg)
+    for steps in (0, 5):
+        h.step(steps)
+        for sp, v in ((0, 2e6), (2, 2e4)):
+            out = h.phase_space(0, sp, 50, 160, -v, v)
+            h.sync()
+            p = h.particles(0, sp)
+            assert np.array_equal(out.cpu().numpy(), O.phase_space(p["z"], p["vz"], cfg["L"], 50, 160, -v, v))
+    h.close()
