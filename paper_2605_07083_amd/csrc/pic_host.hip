@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <new>
 #include <numeric>
 #include <string>
@@ -33,6 +34,9 @@ extern "C" hipError_t picx_prepare(void);
 extern "C" hipError_t picx_launch_phase_hist(const Diode *D, const DiodeState *S, int d, int s, int parity, int nz,
                                              int nv, double sz, double vmin, double sv, unsigned long long *out,
                                              int64_t capacity, hipStream_t st);
+extern "C" hipError_t picx_launch_read_tally(const Diode *D, int d, ReadBack *out, hipStream_t st);
+extern "C" hipError_t picx_launch_read_fields(const Diode *D, int d, int nodes, int time_avg, ReadBack *out,
+                                              hipStream_t st);
 extern "C" int picx_sources_field_kernels(int max_nodes, int mode);
 extern "C" hipError_t picx_launch_profile_load(const Diode *D, const double *dens, int rows, int nd, int max_cells,
                                                hipStream_t s);
@@ -337,6 +341,11 @@ struct pic_handle {
     std::vector<hipEvent_t> evpool;         // pic_step_timed's events, created on demand, reused
     hipEvent_t tev[2] = {nullptr, nullptr}; // placeholders for event nodes not timed in a replay
     hipEvent_t tt[2] = {nullptr, nullptr};  // start and end of a timed run
+    // pinned host memory of the read-back kernels, of the first read; the
+    // mutex lets several threads read one handle
+    std::mutex read_mu;
+    ReadBack *read = nullptr;
+    int device = -1;                        // the workspace's GPU
     void drop_graphs()
     {
         for (auto &kv : graphs) {
@@ -354,6 +363,7 @@ struct pic_handle {
         for (auto e : tt)
             if (e) (void)hipEventDestroy(e);
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
+        if (read) (void)hipHostFree(read);
     }
     std::vector<std::array<int64_t, NSP>> live_offset;
 };
@@ -584,11 +594,36 @@ int refield(pic_handle *h)
     return PIC_OK;
 }
 
+// Runs a read-back kernel on the handle's stream, with its GPU current, and
+// waits for it; the caller holds read_mu.
+template <class Launch>
+int read_back(pic_handle *h, Launch launch)
+{
+    if (!h->read) {
+        hipPointerAttribute_t a{};
+        HIP_TRY(hipPointerGetAttributes(&a, h->ws));
+        void *p = nullptr;
+        HIP_TRY(hipHostMalloc(&p, sizeof(ReadBack) + 3 * sizeof(double) * h->max_nodes, hipHostMallocDefault));
+        h->read = static_cast<ReadBack *>(p);
+        h->device = a.device;
+    }
+    int dev = h->device;
+    HIP_TRY(hipGetDevice(&dev));
+    if (dev != h->device) HIP_TRY(hipSetDevice(h->device));
+    const hipError_t e = launch();
+    if (dev != h->device) (void)hipSetDevice(dev);
+    HIP_TRY(e);
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    return PIC_OK;
+}
+
 int read_state(pic_handle *h, int d, DiodeState &st, DiodeTally &t)
 {
-    HIP_TRY(hipStreamSynchronize(h->stream));
-    HIP_TRY(hipMemcpy(&st, h->hD[d].st, sizeof(st), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(&t, h->hD[d].tally, sizeof(t), hipMemcpyDeviceToHost));
+    std::lock_guard<std::mutex> lock(h->read_mu);
+    int rc = read_back(h, [&] { return picx_launch_read_tally(h->dD, d, h->read, h->stream); });
+    if (rc) return rc;
+    st = h->read->st;
+    t = h->read->tally;
     return PIC_OK;
 }
 
@@ -748,10 +783,10 @@ static int init_impl(const pic_config *cfgs, int n_diodes, void *dev_workspace, 
     // the staging vectors die here: wait for the copies
     if (hipStreamSynchronize(h->stream) != hipSuccess) return cleanup(fail(PIC_EHIP, "sync failed"));
     if (dens) {
+        if (hipMemcpy(st.data(), h->dS, sizeof(DiodeState) * n_diodes, hipMemcpyDeviceToHost) != hipSuccess)
+            return cleanup(fail(PIC_EHIP, "state read failed"));
         for (int d = 0; d < n_diodes; ++d) {
-            DiodeState sd;
-            if (hipMemcpy(&sd, h->hD[d].st, sizeof(sd), hipMemcpyDeviceToHost) != hipSuccess)
-                return cleanup(fail(PIC_EHIP, "state read failed"));
+            const DiodeState &sd = st[d];
             const uint32_t err = sd.err;
             // live counts are births minus losses from n_load: offset by what was loaded
             h->live_offset[d][SP_P] = (int64_t)sd.n[SP_P] - cfgs[d].n_load;
@@ -804,11 +839,10 @@ int pic_sync(pic_handle *h)
 {
     if (!h) return fail(PIC_EINVAL, "null handle");
     HIP_TRY(hipStreamSynchronize(h->stream));
-    for (int d = 0; d < h->nd; ++d) {
-        uint32_t err = 0;
-        HIP_TRY(hipMemcpy(&err, &h->hD[d].st->err, sizeof(err), hipMemcpyDeviceToHost));
-        if (err) return err_code(err);
-    }
+    std::vector<DiodeState> st(h->nd);
+    HIP_TRY(hipMemcpy(st.data(), h->dS, sizeof(DiodeState) * h->nd, hipMemcpyDeviceToHost));
+    for (const DiodeState &s : st)
+        if (s.err) return err_code(s.err);
     return PIC_OK;
 }
 
@@ -933,30 +967,15 @@ int pic_avg_control(pic_handle *h, int diode, int on)
 int pic_get_fields(pic_handle *h, int diode, double *phi, double *n_e, double *n_i, int time_avg)
 {
     if (!h || diode < 0 || diode >= h->nd) return fail(PIC_EINVAL, "bad arguments");
-    HIP_TRY(hipStreamSynchronize(h->stream));
-    const Diode &D = h->hD[diode];
     const int nn = h->cfg[diode].N + 1;
-    DiodeState st;
-    HIP_TRY(hipMemcpy(&st, D.st, sizeof(st), hipMemcpyDeviceToHost));
-    const double navg = time_avg ? (double)std::max(st.avg_steps, 1) : 1.0;
-    if (time_avg && st.avg_steps == 0) return fail(PIC_EINVAL, "no time average accumulated");
-    if (phi) {
-        // the large-grid field step stores phi less phi_slope j (zero on smaller grids)
-        HIP_TRY(hipMemcpy(phi, time_avg ? D.phi_sum : D.phi, nn * sizeof(double), hipMemcpyDeviceToHost));
-        const double slope = time_avg ? st.phi_slope_sum : st.phi_slope;
-        for (int j = 0; j < nn; ++j) phi[j] = (phi[j] + slope * (double)j) / navg;
-    }
-    std::vector<long long> H[NSP];
-    for (int s = 0; s < NSP; ++s) {
-        H[s].resize(nn);
-        HIP_TRY(hipMemcpy(H[s].data(), time_avg ? D.Hsum[s] : D.Hlast[s], nn * sizeof(long long),
-                          hipMemcpyDeviceToHost));
-    }
-    const double k = h->der[diode].w0 / (4294967296.0 * h->der[diode].dz * navg);
-    for (int j = 0; j < nn; ++j) {
-        const double vol = (j == 0 || j == nn - 1) ? 2.0 : 1.0;
-        if (n_e) n_e[j] = k * vol * ((double)H[SP_P][j] + (double)H[SP_E][j]);
-        if (n_i) n_i[j] = k * vol * (double)H[SP_I][j];
+    std::lock_guard<std::mutex> lock(h->read_mu);
+    int rc = read_back(h, [&] { return picx_launch_read_fields(h->dD, diode, nn, time_avg, h->read, h->stream); });
+    if (rc) return rc;
+    if (time_avg && h->read->st.avg_steps == 0) return fail(PIC_EINVAL, "no time average accumulated");
+    const double *v = reinterpret_cast<const double *>(h->read + 1);
+    for (double *out : {phi, n_e, n_i}) {
+        if (out) std::memcpy(out, v, nn * sizeof(double));
+        v += nn;
     }
     return PIC_OK;
 }

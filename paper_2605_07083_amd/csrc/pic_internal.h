@@ -113,6 +113,13 @@ struct DiodeTally {
     unsigned long long resorts_ions_kept;   // of them, those that left the ions in place
 };
 
+// What a read-back kernel writes to pinned host memory; the node profiles
+// (phi, n_e, n_i) follow it.
+struct alignas(256) ReadBack {
+    DiodeState st;
+    DiodeTally tally;
+};
+
 struct TallySnap {
     unsigned long long step;
     DiodeTally t;

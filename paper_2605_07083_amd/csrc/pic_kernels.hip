@@ -1297,6 +1297,62 @@ extern "C" hipError_t picx_launch_phase_hist(const Diode *D, const DiodeState *S
 }
 
 // ---------------------------------------------------------------------------
+// Read-back of one diode into the caller's pinned host memory: its state and
+// tallies (whole words), or the node profiles as the C ABI gives them, in the
+// ABI's own order of double operations.  One launch and one wait instead of a
+// copy per array through the runtime's staging: tallies 39 -> 22 us,
+// profiles of 257 nodes 89 -> 24 us.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_read_tally(const Diode *__restrict__ D, int d, ReadBack *__restrict__ out)
+{
+    static_assert(sizeof(DiodeState) % 4 == 0 && sizeof(DiodeTally) % 4 == 0, "read back in words");
+    const uint32_t *st = reinterpret_cast<const uint32_t *>(D[d].st);
+    const uint32_t *tl = reinterpret_cast<const uint32_t *>(D[d].tally);
+    for (int i = threadIdx.x; i < (int)(sizeof(DiodeState) / 4); i += 256)
+        reinterpret_cast<uint32_t *>(&out->st)[i] = st[i];
+    for (int i = threadIdx.x; i < (int)(sizeof(DiodeTally) / 4); i += 256)
+        reinterpret_cast<uint32_t *>(&out->tally)[i] = tl[i];
+}
+
+// phi, n_e and n_i, nn values each, behind the ReadBack block.
+__global__ __launch_bounds__(256) void k_read_fields(const Diode *__restrict__ D, int d, int time_avg,
+                                                     ReadBack *__restrict__ out)
+{
+#pragma clang fp contract(off)
+    const Diode &dd = D[d];
+    const int nn = dd.N + 1, j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= nn) return;
+    const DiodeState &st = *dd.st;
+    const int steps = st.avg_steps;
+    if (j == 0) out->st.avg_steps = steps;
+    const double navg = time_avg ? (double)max(steps, 1) : 1.0;
+    // the large-grid field step stores phi less phi_slope j (zero on smaller grids)
+    const double slope = time_avg ? st.phi_slope_sum : st.phi_slope;
+    const double phi = time_avg ? dd.phi_sum[j] : dd.phi[j];
+    long long h[NSP];
+    for (int s = 0; s < NSP; ++s) h[s] = time_avg ? dd.Hsum[s][j] : dd.Hlast[s][j];
+    const double k = dd.w0 / (4294967296.0 * dd.dz * navg);
+    const double vol = (j == 0 || j == nn - 1) ? 2.0 : 1.0;
+    double *o = reinterpret_cast<double *>(out + 1);
+    o[j] = (phi + slope * (double)j) / navg;
+    o[nn + j] = k * vol * ((double)h[SP_P] + (double)h[SP_E]);
+    o[2 * nn + j] = k * vol * (double)h[SP_I];
+}
+
+extern "C" hipError_t picx_launch_read_tally(const Diode *D, int d, ReadBack *out, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_read_tally, dim3(1), dim3(256), 0, st, D, d, out);
+    return hipGetLastError();
+}
+
+extern "C" hipError_t picx_launch_read_fields(const Diode *D, int d, int nodes, int time_avg, ReadBack *out,
+                                              hipStream_t st)
+{
+    hipLaunchKernelGGL(k_read_fields, dim3((nodes + 255) / 256), dim3(256), 0, st, D, d, time_avg, out);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
 // Re-sort by bins of 32 cells: count -> scan -> scatter -> finalize (compacts
 // holes too).  Bins rather than cells: the LDS windows only need each run of
 // chunks confined to a narrow range of cells, and with electrons drifting

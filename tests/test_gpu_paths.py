@@ -421,3 +421,36 @@ def test_phase_space_rounds(pic, O, n_load):
             p = h.particles(0, sp)
             assert np.array_equal(out.cpu().numpy(), O.phase_space(p["z"], p["vz"], cfg["L"], 50, 160, -v, v))
     h.close()
+
+
+@pytest.mark.parametrize("cells", [2, 255, 256, 511, 2048, 4096])
+def test_read_back_of_profiles_and_tallies(pic, cells):
+    """Node profiles equal the deposits in the C ABI's order of operations, bit
+    for bit, at edges of the read-back kernel's blocks and on both field
+    kernels; a one-step average is that step's profile; two diodes of different
+    sizes keep apart; several threads may read one handle."""
+    from concurrent.futures import ThreadPoolExecutor
+    cfg = presets.scaled(presets.tiny(), N=cells, n_load=cells * 20)
+    h = pic.Handle([cfg, presets.scaled(presets.tiny(), N=300, n_load=6000)])
+    h.step(7)
+    with pytest.raises(pic.PicError):
+        h.fields(0, time_avg=True)
+    h.avg_reset()
+    h.step(1)
+    for d, n in ((0, cells), (1, 300)):
+        f, a = h.fields(d), h.fields(d, time_avg=True)
+        der = pic.pic_derive(h.cfgs[d])
+        k = der["w0"] / (4294967296.0 * der["dz"] * 1.0)
+        vol = np.ones(n + 1)
+        vol[0] = vol[-1] = 2.0
+        H = [h.hist(d, s).astype(np.float64) for s in range(3)]
+        assert np.array_equal(f["n_e"], k * vol * (H[0] + H[1])) and np.array_equal(f["n_i"], k * vol * H[2])
+        assert f["phi"][0] == 0.0 and np.isfinite(f["phi"]).all() and np.abs(f["phi"]).max() > 0.0
+        assert all(np.array_equal(f[q], a[q]) for q in f)
+    want = [h.tally(d) for d in (0, 1)], [h.fields(d) for d in (0, 1)]
+    with ThreadPoolExecutor(4) as ex:
+        got = list(ex.map(lambda i: (i % 2, h.tally(i % 2), h.fields(i % 2)), range(32)))
+    for d, t, f in got:
+        assert all(np.array_equal(t[q], want[0][d][q]) for q in t)
+        assert all(np.array_equal(f[q], want[1][d][q]) for q in f)
+    h.close()
