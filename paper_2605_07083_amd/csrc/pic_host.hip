@@ -584,10 +584,14 @@ int run_steps(pic_handle *h, int64_t nsteps)
     return PIC_OK;
 }
 
-int refield(pic_handle *h)
+// Deposit and field of the particles as they are; sorted: they are in cell
+// order already (the profile loader's).
+int refield(pic_handle *h, bool sorted)
 {
-    HIP_TRY(picx_launch_sort(h->dD, h->dS, h->nd, h->ppt, h->grid, h->parity, h->stream));
-    h->parity ^= 1;
+    if (!sorted) {
+        HIP_TRY(picx_launch_sort(h->dD, h->dS, h->nd, h->ppt, h->grid, h->parity, h->stream));
+        h->parity ^= 1;
+    }
     HIP_TRY(picx_launch_particles(h->dD, h->dS, h->nd, 1, h->ppt, h->grid, h->parity, h->stream));
     HIP_TRY(picx_launch_sources_field(h->dD, h->dS, h->nd, 1, h->max_nodes, h->parity, h->stream));
     h->sort_next = false;
@@ -801,7 +805,7 @@ static int init_impl(const pic_config *cfgs, int n_diodes, void *dev_workspace, 
                                                       "(raise capacity_factor or n_load)"));
         }
     }
-    rc = refield(h);
+    rc = refield(h, dens != nullptr);
     if (rc) return cleanup(rc);
     *out = h;
     return PIC_OK;
@@ -1129,7 +1133,7 @@ int pic_set_counters(pic_handle *h, int diode, int64_t step, uint32_t next_id)
 int pic_refield(pic_handle *h)
 {
     if (!h) return fail(PIC_EINVAL, "null handle");
-    return refield(h);
+    return refield(h, false);
 }
 
 int pic_step_timed(pic_handle *h, int64_t nsteps, double *particle_kernel_ms, double *total_ms)

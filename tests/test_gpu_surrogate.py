@@ -341,6 +341,31 @@ def test_state_load_batched_and_errors(torch, O):
         pic.Handle(cfgs[0], state=torch.zeros((1, 3, 256), dtype=torch.float64, device="cuda:0"))
 
 
+@pytest.mark.parametrize("cells,per_cell", [(2, 40), (7, 900), (8, 200), (9, 3), (101, 1), (257, 40)])
+def test_state_load_over_the_blocks_of_cells(torch, O, cells, per_cell):
+    """The loader deals eight cells at a time: grids around that, cells without
+    particles and cells of several rounds, against the oracle; the loaded
+    stores count as sorted, and steps and re-sorts go on from them."""
+    from paper_2605_07083_amd import pic
+    cfg = presets.scaled(presets.tiny(), gamma_emit=1e21, N=cells, n_load=cells * per_cell, capacity_factor=3.0)
+    st = _state(cfg, 40 + cells)
+    st[:2, 3:5] = 0.0
+    h = pic.Handle(cfg, state=torch.tensor(st[None], dtype=torch.float64, device="cuda:0"))
+    g, t = gpu_state(h, 0)
+    s = O.Sim(cfg)
+    s.load_state(st)
+    for sp in (0, 2):
+        a, o = by_id(g[sp]), by_id(s.particles(sp))
+        assert np.array_equal(a["id"], o["id"]) and np.array_equal(a["z"], o["z"])
+        assert np.array_equal(a["tc"], o["tc"])
+        for c in ("vx", "vy", "vz"):
+            assert np.max(np.abs(a[c] - o[c].astype(np.float32)) / np.abs(o[c]).max()) < 1e-6, (sp, c)
+    assert h.tally(0)["resorts"] == 1
+    assert deposit_matches(O, cfg, h, g, 0) == []
+    assert restart_step_check(O, cfg, h, 70) == []
+    h.close()
+
+
 @pytest.mark.parametrize("B,X", [(1, 64), (2, 128), (9, 320), (20, 704), (70, 64), (5, 4096), (33, 1216), (64, 2048)])
 def test_forward_is_the_same_on_every_tiling(sur, torch, B, X):
     """Rows per block follow the batch and the length (32 to 192, the last tile
