@@ -84,7 +84,6 @@ __device__ __forceinline__ void put_cold(GLB ColdRec *p, float vx, float vy, uin
     *(GLB u32x4 *)p = u32x4{__float_as_uint(vx), __float_as_uint(vy), id, 0u};
 }
 constexpr int FT = 1024;           // threads of the sources / field blocks
-constexpr int FW = FT / 64;
 constexpr double TWO32 = 4294967296.0;
 
 // ---------------------------------------------------------------------------
@@ -620,37 +619,65 @@ __device__ __forceinline__ void flush_tally(const Diode &dd, RareTally *t, int l
     }
 }
 
-// Fold the accumulator copies (one per lane of the first wave, read by
-// read_tally_copy) into rt (LDS) with a fixed shuffle tree per field.
-__device__ __forceinline__ void fold_tally_copies(RareTally v, RareTally *rt)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double x)
 {
-    if (threadIdx.x >= 64) return;
-    const int lane = threadIdx.x;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Sums over the wave, in its last lane.
+__device__ __forceinline__ float wave_sum_f32(float x)
+{
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), DPP_ROW_SHR1, 0xf, 0xf, true));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), DPP_ROW_SHR2, 0xf, 0xf, true));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), DPP_ROW_SHR4, 0xf, 0xf, true));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), DPP_ROW_SHR8, 0xf, 0xf, true));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), DPP_ROW_BCAST15, 0xa, 0xf, true));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), DPP_ROW_BCAST31, 0xc, 0xf, true));
+    return x;
+}
+__device__ __forceinline__ double wave_sum_f64(double x)
+{
+    x += dpp_f64<DPP_ROW_SHR1, 0xf>(x);
+    x += dpp_f64<DPP_ROW_SHR2, 0xf>(x);
+    x += dpp_f64<DPP_ROW_SHR4, 0xf>(x);
+    x += dpp_f64<DPP_ROW_SHR8, 0xf>(x);
+    x += dpp_f64<DPP_ROW_BCAST15, 0xa>(x);
+    x += dpp_f64<DPP_ROW_BCAST31, 0xc>(x);
+    return x;
+}
+
+// Fold the accumulator copies (one per lane of the first wave, read by
+// read_tally_copy) into rt (LDS) with a fixed tree per field: cross-lane adds
+// in the vector ALU (the 132 shuffles through LDS took 2 us).
+__device__ __forceinline__ void fold_tally_copies(const RareTally &v, RareTally *rt)
+{
+    const bool last = threadIdx.x == 63;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) v.cand[k] += __shfl_xor(v.cand[k], o, 64);
-#pragma unroll
-        for (int k = 0; k < NCH; ++k) v.coll[k] += __shfl_xor(v.coll[k], o, 64);
-#pragma unroll
-        for (int sp = 0; sp < NSP; ++sp)
-#pragma unroll
-            for (int w = 0; w < 2; ++w) {
-                v.abs_count[sp][w] += __shfl_xor(v.abs_count[sp][w], o, 64);
-                v.abs_energy[sp][w] += __shfl_xor(v.abs_energy[sp][w], o, 64);
-            }
-        v.ion_lost += __shfl_xor(v.ion_lost, o, 64);
+    for (int k = 0; k < 2; ++k) {
+        const int t = wave_incl_scan_i32((int)v.cand[k]);
+        if (last) rt->cand[k] = (unsigned)t;
     }
-    if (lane == 0) {
-        for (int k = 0; k < 2; ++k) rt->cand[k] += v.cand[k];
-        for (int k = 0; k < NCH; ++k) rt->coll[k] += v.coll[k];
-        for (int sp = 0; sp < NSP; ++sp)
-            for (int w = 0; w < 2; ++w) {
-                rt->abs_count[sp][w] += v.abs_count[sp][w];
-                rt->abs_energy[sp][w] += v.abs_energy[sp][w];
-            }
-        rt->ion_lost += v.ion_lost;
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) {
+        const int t = wave_incl_scan_i32((int)v.coll[k]);
+        if (last) rt->coll[k] = (unsigned)t;
     }
+#pragma unroll
+    for (int sp = 0; sp < NSP; ++sp)
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            const int t = wave_incl_scan_i32((int)v.abs_count[sp][w]);
+            const double e = wave_sum_f64(v.abs_energy[sp][w]);
+            if (last) {
+                rt->abs_count[sp][w] = (unsigned)t;
+                rt->abs_energy[sp][w] = e;
+            }
+        }
+    const int t = wave_incl_scan_i32(v.ion_lost);
+    if (last) rt->ion_lost = t;
 }
 
 // Add a step's tally to the diode's cumulative tallies (one thread; atomics
@@ -670,6 +697,22 @@ __device__ __forceinline__ void apply_tally(const Diode &dd, const RareTally &t)
                 atomicAdd(&T->abs_count[sp][w], (unsigned long long)t.abs_count[sp][w]);
                 atomicAdd(&T->abs_energy[sp][w], t.abs_energy[sp][w]);
             }
+}
+
+// apply_tally by the first wave, a lane per field.
+__device__ __forceinline__ void apply_tally_wave(const Diode &dd, const RareTally &t, int lane)
+{
+    static_assert(offsetof(RareTally, coll) == 8 && offsetof(RareTally, abs_count) == 8 + 4 * NCH, "lanes by field");
+    DiodeTally *T = dd.tally;
+    constexpr int C = 2 + NCH, A = C + 2 * NSP;
+    if (lane < A) {
+        const unsigned v = reinterpret_cast<const unsigned *>(&t)[lane];
+        unsigned long long *p = lane < 2 ? &T->cand[lane] : lane < C ? &T->coll[lane - 2] : &T->abs_count[0][0] + (lane - C);
+        if (v) atomicAdd(p, (unsigned long long)v);
+    } else if (lane >= 32 && lane < 32 + 2 * NSP) {
+        const int k = lane - 32;
+        if ((&t.abs_count[0][0])[k]) atomicAdd(&T->abs_energy[0][0] + k, (&t.abs_energy[0][0])[k]);
+    }
 }
 
 // The diode's counters, one lane of the calling wave per 32-bit field, read
@@ -1817,53 +1860,6 @@ __device__ __forceinline__ I128 wave_incl_scan_i128(I128 x)
 // phi_j = V j / N + alpha (j T_N - N T_j) / N: the direct solution of the
 // constant-coefficient Dirichlet system, rounded once at the end.
 // ---------------------------------------------------------------------------
-// Block scans of the per-thread totals of the first NWV waves (the other
-// waves pass zeros and only take part in the barriers), for the field kernels
-// whose threads each walk consecutive nodes serially in registers.
-template <int NWV>
-__device__ __forceinline__ long long block_scan_excl_i64(long long v, long long *sh, long long &total)
-{
-    const int lane = lane_id(), w = threadIdx.x >> 6;
-    long long incl = 0;
-    if (w < NWV) {
-        incl = wave_incl_scan_i64(v);
-        if (lane == 63) sh[w] = incl;
-    }
-    __syncthreads();
-    long long off = 0, tot = 0;
-#pragma unroll
-    for (int q = 0; q < NWV; ++q) {
-        const long long t = sh[q];
-        if (q < w) off += t;
-        tot += t;
-    }
-    __syncthreads();
-    total = tot;
-    return off + incl - v;
-}
-
-template <int NWV>
-__device__ __forceinline__ I128 block_scan_excl_i128(I128 v, I128 *sh, I128 &total)
-{
-    const int lane = lane_id(), w = threadIdx.x >> 6;
-    I128 incl = i128(0);
-    if (w < NWV) {
-        incl = wave_incl_scan_i128(v);
-        if (lane == 63) sh[w] = incl;
-    }
-    __syncthreads();
-    I128 off = i128(0), tot = i128(0);
-#pragma unroll
-    for (int q = 0; q < NWV; ++q) {
-        const I128 t = sh[q];
-        if (q < w) off = add(off, t);
-        tot = add(tot, t);
-    }
-    __syncthreads();
-    total = tot;
-    return add(off, add(incl, neg(v)));
-}
-
 // ---------------------------------------------------------------------------
 // Sources and field of a step in one kernel per step.
 //
@@ -1880,6 +1876,15 @@ __device__ __forceinline__ I128 block_scan_excl_i128(I128 v, I128 *sh, I128 &tot
 // and the record block has written its tallies (a counter they bump), while
 // the tiles solve.  Every wait is on blocks of the same diode dispatched
 // earlier.
+//
+// Bound by latency, a chain of some 6 us per tile block (2049 nodes, in us):
+// the first reads 2.1, all requested at once, with the tally fold, the counters
+// and the emission draw on waves of their own meanwhile; plan 0.4; newborns'
+// charge 1.0; the scans 1.4, three barriers; potential 0.6, stores 0.5.  With
+// the reads in loops, the draw in the plan and 128-bit scans it took 8.5 us
+// (tail block 7.7, now 4.6): a step of the 2048-cell diode 23.2 -> 21.0 us.
+// The plan and the tail are inlined: as calls they address LDS through flat
+// pointers, and a step took 1.7 us more.
 //
 //   k_field_step   (N + 1 <= FUSED_MAX_NODES) tiles of TILE nodes; every tile
 //                  block stages the charge of every node in LDS and runs the
@@ -1907,6 +1912,9 @@ constexpr int FUSED_MAX_NODES = 2049;
 // nodes per tile block of k_field_tiles (one per thread of its first half:
 // the per-node work of a tile runs on one CU, so smaller tiles spread it)
 constexpr int BIG_TILE = FIELD_BIG_TILE;
+// k_field_step's scans: threads of SCAN_WAVES waves, SCAN_PER interior nodes each.
+constexpr int SCAN_WAVES = 8, SCAN_PER = 4, SCAN_NODES = SCAN_WAVES * 64 * SCAN_PER;
+static_assert(FUSED_MAX_NODES - 2 <= SCAN_NODES, "every interior node has a thread");
 static_assert(2 * BIG_TILE <= FT && BIG_TILE % 64 == 0, "one thread per node of a tile, whole waves, and as many waves again for the node bookkeeping");
 constexpr int MAX_TILES = 32768 / BIG_TILE;    // N <= 32767: the earlier tiles fit one wave
 static_assert(MAX_TILES <= 64, "one lane per earlier tile");
@@ -1927,7 +1935,7 @@ struct BirthPlan {
 // memory on the step's critical path (the particle kernel before has evicted
 // them from the caches).
 struct BirthConsts {
-    double L, invdz, dt, emit_x, sig_c;
+    double L, invdz, dt, sig_c;
     const IzEvent *izq;
     uint32_t kseed;
     int N, replenish;
@@ -1939,7 +1947,6 @@ __device__ __forceinline__ void birth_consts(const Diode &dd, BirthConsts &bc)
     bc.L = dd.L;
     bc.invdz = dd.invdz;
     bc.dt = dd.dt;
-    bc.emit_x = dd.emit_x;
     bc.sig_c = dd.sig_c;
     bc.izq = dd.izq;
     bc.kseed = dd.kseed;
@@ -2104,49 +2111,57 @@ struct FieldShared {
     DiodeState s_st;           // the counters as this block read them
     BirthPlan bp;
     BirthConsts bc;
+    int ne;                    // electrons emitted this step
 };
 
-// The first reads of every block of a field step (mode 0): the particle
-// kernel's tally copies (first wave) and the counters (second wave).
-__device__ __forceinline__ RareTally field_step_reads(const Diode &dd, FieldShared &fs)
-{
-    const int tid = threadIdx.x;
-    RareTally copy{};
-    if (tid < 64) copy = read_tally_copy(dd);
-    if (tid >= 64 && tid < 128) load_state(dd.st, &fs.s_st);
-    if (tid == 192) birth_consts(dd, fs.bc);
-    if (tid == 0) {
-        rare_tally_zero(&fs.rt);
-        rare_tally_zero(&fs.rs);
-    }
-    return copy;
-}
-
-// After field_step_reads and a barrier: the tail block folds every tally
-// copy into fs.rt, the others only the ions lost; the spilled rare items are
-// worked off (record block) or waited for; once a tile block or the record
-// block is done with the counters it bumps st->arrive, then every block works
-// out the plan of the step's births and, when the plan needs it, the
-// ionisation events in parent-id order in keys.
 // The roles of a field step's blocks (mode 0): block 0 writes the newborn
 // records, blocks 1..T take the node tiles, block T + 1 (dispatched last)
 // applies the step's tallies and advances the counters.
 enum FieldRole { ROLE_RECORDS, ROLE_TILE, ROLE_TAIL };
 
-__device__ void field_step_plan(const Diode &dd, int parity, uint32_t step, FieldRole role, RareTally copy,
-                                FieldShared &fs, unsigned long long *keys)
+// The first reads of every block of a field step (mode 0): the particle
+// kernel's tally copies (first wave), folded at once -- every field by the tail
+// block, the ions lost by the others -- the counters (second wave), and the
+// step's emitted electrons, whose draw needs only the step (fourth wave).
+// Each in its own wave, so that they pass while the tiles' deposits arrive.
+__device__ __forceinline__ void field_step_reads(const Diode &dd, FieldShared &fs, FieldRole role)
+{
+    const int tid = threadIdx.x;
+    if (tid < 64) {
+        const RareTally copy = read_tally_copy(dd);
+        if (tid == 0) rare_tally_zero(&fs.rs);
+        if (role == ROLE_TAIL) {
+            fold_tally_copies(copy, &fs.rt);
+        } else {
+            const int v = wave_incl_scan_i32(copy.ion_lost);
+            if (tid == 63) fs.rt.ion_lost = v;
+        }
+    }
+    if (tid >= 64 && tid < 128) load_state(dd.st, &fs.s_st);
+    if (tid == 192) {
+        const uint32_t step = __hip_atomic_load(glb(&dd.st->step), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        birth_consts(dd, fs.bc);
+        int ne = 0;
+        if (dd.emit_x > 0.0) {
+            const double fl = floor(dd.emit_x);
+            const uint4 be = philox(step, EV_EMIT, 0u, 0u, 0xFFFFFFFFu, dd.kseed);
+            ne = (int)fl + (u53(be.x, be.y) < dd.emit_x - fl ? 1 : 0);
+        }
+        fs.ne = ne;
+    }
+}
+
+// After field_step_reads and a barrier: the spilled rare items are worked off
+// (record block) or waited for; once a tile block or the record block is done
+// with the counters it bumps st->arrive, then every block works out the plan
+// of the step's births and, when the plan needs it, the ionisation events in
+// parent-id order in keys.
+__device__ __forceinline__ void field_step_plan(const Diode &dd, int parity, uint32_t step, FieldRole role, FieldShared &fs,
+                                unsigned long long *keys)
 {
     DiodeState *st = dd.st;
     const int tid = threadIdx.x;
     const bool records = role == ROLE_RECORDS;
-    if (__builtin_expect(role == ROLE_TAIL, 0)) {
-        fold_tally_copies(copy, &fs.rt);      // the step's totals, applied by the tail block
-    } else if (tid < 64) {
-        int v = copy.ion_lost;                // the others need the ions lost only
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (tid == 0) fs.rt.ion_lost = v;
-    }
     if (__builtin_expect((fs.s_st.rare_n[SP_P] | fs.s_st.rare_n[SP_E] | fs.s_st.rare_n[SP_I]) != 0, 0)) {
         // items the particle kernel's queues could not hold: the record
         // block collides them (they may queue ionisations and lose ions),
@@ -2172,8 +2187,8 @@ __device__ void field_step_plan(const Diode &dd, int parity, uint32_t step, Fiel
         }
         __syncthreads();
         if (tid >= 64 && tid < 128) load_state(st, &fs.s_st);
+        __syncthreads();
     }
-    __syncthreads();
     if (tid == 0) {
         // this tile or record block is done with the counters and the copies
         if (role != ROLE_TAIL) __hip_atomic_fetch_add(glb(&st->arrive), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2181,12 +2196,7 @@ __device__ void field_step_plan(const Diode &dd, int parity, uint32_t step, Fiel
         BirthPlan p;
         p.q = min(S.iz_count, IZQ_CAP);
         p.R = fs.bc.replenish ? S.ion_lost + fs.rt.ion_lost : 0;
-        p.ne = 0;
-        if (fs.bc.emit_x > 0.0) {
-            const double fl = floor(fs.bc.emit_x);
-            const uint4 be = philox(step, EV_EMIT, 0u, 0u, 0xFFFFFFFFu, fs.bc.kseed);
-            p.ne = (int)fl + (u53(be.x, be.y) < fs.bc.emit_x - fl ? 1 : 0);
-        }
+        p.ne = fs.ne;
         p.id0 = S.next_id;
         p.bP = S.n[SP_P];
         p.bE = S.n[SP_E];
@@ -2229,7 +2239,7 @@ __device__ void field_step_plan(const Diode &dd, int parity, uint32_t step, Fiel
 // copies: the copies cleared, the step's tallies applied, the counters
 // advanced; on a snapshot step, once the record block has also released its
 // tallies (newborns placed beyond the anode), the snapshot taken.
-__device__ void field_step_tail(const Diode &dd, FieldShared &fs, uint32_t step, int avg, int others)
+__device__ __forceinline__ void field_step_tail(const Diode &dd, FieldShared &fs, uint32_t step, int avg, int others)
 {
     DiodeState *st = dd.st;
     const int tid = threadIdx.x;
@@ -2239,11 +2249,13 @@ __device__ void field_step_tail(const Diode &dd, FieldShared &fs, uint32_t step,
         __hip_atomic_store(glb(&st->arrive), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (tid < 64) dd.tacc[tid].t = RareTally{};
+    if (tid < 64) {
+        dd.tacc[tid].t = RareTally{};
+        apply_tally_wave(dd, fs.rt, tid);
+    }
     if (tid == 0) {
         const BirthPlan &p = fs.bp;
         if (p.okP < p.q + p.R || p.okE < p.ne || p.okI < p.q + p.R) atomicOr(&st->err, ERR_CAPACITY);
-        apply_tally(dd, fs.rt);
         st->n[SP_P] = p.bP + p.okP;
         st->n[SP_E] = p.bE + p.okE;
         st->n[SP_I] = p.bI + p.okI;
@@ -2267,7 +2279,7 @@ __device__ void field_step_tail(const Diode &dd, FieldShared &fs, uint32_t step,
         // the record block (dispatched before this block) sets the flag
         while (__hip_atomic_load(glb(&st->rec_flag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != nstep)
             __builtin_amdgcn_s_sleep(2);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");   // and this wave's updates are done
         TallySnap &sn = dd.ring[(nstep / (uint32_t)dd.tally_period) % RING];
         sn.step = nstep;
         sn.t = *dd.tally;
@@ -2342,19 +2354,19 @@ __device__ __forceinline__ void field_node_phi(const TileConsts &fc, const doubl
 __device__ __forceinline__ void clear_node_hist(const TileConsts &fc)
 {
     const int nn = fc.N + 1;
-    for (int x = threadIdx.x; x < NSP * nn; x += FT) {
-        const int s = x / nn;
-        glb(fc.H[s])[x - s * nn] = 0ull;
-    }
+#pragma unroll
+    for (int s = 0; s < NSP; ++s)
+        for (int j = threadIdx.x; j < nn; j += FT) glb(fc.H[s])[j] = 0ull;
 }
 
 __global__ __launch_bounds__(FT) void k_field_step(const Diode *__restrict__ D, int mode, int parity)
 {
-    __shared__ long long R[FUSED_MAX_NODES];          // the charge of every node
+    __shared__ __align__(16) long long R[SCAN_NODES];    // the charge of every interior node (node j at j - 1)
     __shared__ unsigned long long keys[IZQ_CAP];      // ionisation events by parent id
     __shared__ unsigned long long hb[NSP][TILE];      // the own tile's deposits per species
-    __shared__ long long sh64[FW];
-    __shared__ I128 sh128[FW];
+    __shared__ long long sh_s1[SCAN_WAVES];           // per scanning wave: sum of R,
+    __shared__ float sh_mag[SCAN_WAVES];              //   of |R|,
+    __shared__ I128 sh_t[SCAN_WAVES];                 //   of S1
     __shared__ double ph[TILE + 2];                   // phi on the own tile and its halo
     __shared__ I128 tT[TILE + 2];                     // T_j on the own tile and its halo
     __shared__ FieldShared fs;
@@ -2371,30 +2383,48 @@ __global__ __launch_bounds__(FT) void k_field_step(const Diode *__restrict__ D, 
     const int a0 = t * TILE, b0 = min(nn, a0 + TILE);
     const int tid = threadIdx.x;
 
-    // the counters and the particle kernel's tally copies; tile blocks load
-    // every node's charge and their own tile's deposits meanwhile
-    RareTally copy{};
-    if (mode == 0) copy = field_step_reads(dd, fs);
+    // tile blocks load every interior node's deposits, two nodes per thread
+    // and the boundary nodes apart, all requested at once (a loop over the
+    // nodes waited for memory three times); the counters and the particle
+    // kernel's tally copies meanwhile
+    static_assert(SCAN_NODES == 2 * FT, "two interior nodes per thread");
+    unsigned long long h[2][NSP], hbound[NSP];
+    const int jb = tid & 1 ? N : 0;
+    const bool bound = tid >= FT - 2 && jb >= a0 && jb < b0;
+    if (tile) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int s = 0; s < NSP; ++s) h[i][s] = glb(dd.H[s])[min(1 + tid + i * FT, N - 1)];
+        if (bound) {
+#pragma unroll
+            for (int s = 0; s < NSP; ++s) hbound[s] = glb(dd.H[s])[jb];
+        }
+    }
+    if (mode == 0) field_step_reads(dd, fs, role);
     if (tid == 128) tile_consts(dd, fc);
     // whether the step is averaged (the host sets avg_on between steps)
     if (tid == 1) s_avg = __hip_atomic_load(glb(&st->avg_on), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t step = mode == 0 ? (uint32_t)uni((int)st->step) : 0u;
     if (tile) {
-        for (int j = tid; j < nn; j += FT) {
-            long long r = 0;
-            if (j >= 1 && j <= N - 1)
-                r = (long long)(glb(dd.H[SP_I])[j] - glb(dd.H[SP_P])[j] - glb(dd.H[SP_E])[j]);
-            R[j] = r;
-        }
-        for (int i = tid; i < b0 - a0; i += FT) {
 #pragma unroll
-            for (int s = 0; s < NSP; ++s) hb[s][i] = glb(dd.H[s])[a0 + i];
+        for (int i = 0; i < 2; ++i) {
+            const int j = 1 + tid + i * FT;
+            R[j - 1] = j <= N - 1 ? (long long)(h[i][SP_I] - h[i][SP_P] - h[i][SP_E]) : 0;
+            if (j >= a0 && j < min(b0, N)) {
+#pragma unroll
+                for (int s = 0; s < NSP; ++s) hb[s][j - a0] = h[i][s];
+            }
+        }
+        if (bound) {
+#pragma unroll
+            for (int s = 0; s < NSP; ++s) hb[s][jb - a0] = hbound[s];
         }
     }
-    const uint32_t step = mode == 0 ? (uint32_t)uni((int)st->step) : 0u;
     __syncthreads();
     const int avg = uni(s_avg);
     if (mode == 0) {
-        field_step_plan(dd, parity, step, role, copy, fs, keys);
+        field_step_plan(dd, parity, step, role, fs, keys);
         if (__builtin_expect(records, 0)) {
             // the newborns' records and tallies; the flag releases the
             // tallies to the tail block, which waits for them only when the
@@ -2412,7 +2442,7 @@ __global__ __launch_bounds__(FT) void k_field_step(const Diode *__restrict__ D, 
             clear_node_hist(fc);
             return;
         }
-        births_deposit<TILE>(fs.bc, fs.bp, keys, step, R, 0, nn, hb, a0, b0);
+        births_deposit<TILE>(fs.bc, fs.bp, keys, step, R, 1, N, hb, a0, b0);
         __syncthreads();
     } else {
         // refield (no tail block): the last tile block to arrive, once every
@@ -2428,33 +2458,96 @@ __global__ __launch_bounds__(FT) void k_field_step(const Diode *__restrict__ D, 
 
     // phi_j = V j / N + alpha (j T_N - N T_j) / N with the exact sums
     // S1_j = sum_{k<=j} R_k and T_j = sum_{m=1..j-1} S1_m.  The sums run on
-    // the first SCAN_WAVES waves, each thread walking `per` consecutive nodes
-    // serially (serial adds cost less than wave-wide steps of more waves);
-    // the T_j of the own tile and its halo go to LDS, and the potential is
-    // then worked out one node per thread.
-    constexpr int SCAN_WAVES = 8;
-    const int per = (nn + SCAN_WAVES * 64 - 1) / (SCAN_WAVES * 64);
-    const int j0 = tid < SCAN_WAVES * 64 ? tid * per : nn, j1 = min(nn, j0 + per);
-    long long loc = 0;
-    for (int j = j0; j < j1; ++j) loc += R[j];
-    long long tot;
-    const long long s1off = block_scan_excl_i64<SCAN_WAVES>(loc, sh64, tot);
-    I128 tl = i128(0);
-    {
-        long long S1 = s1off;
-        for (int j = j0; j < j1; ++j) {
-            S1 += R[j];
-            if (j >= 1 && j <= N - 1) tl = add(tl, i128(S1));
+    // the first SCAN_WAVES waves, each thread with SCAN_PER consecutive
+    // interior nodes in registers (serial adds cost less than wave-wide steps
+    // of more waves); the T_j of the own tile and its halo go to LDS, and the
+    // potential is then worked out one node per thread.  Where the sum of |R|
+    // times N leaves a bit of 64 spare, no T_j overflows and the second scan
+    // is one of 64-bit integers: the same sums in a third of the adds.
+    const int w = tid >> 6, lane = tid & 63, k0 = tid * SCAN_PER;
+    long long s1[SCAN_PER], inc1 = 0, loc = 0;
+    if (w < SCAN_WAVES) {
+        float mag = 0.0f;
+#pragma unroll
+        for (int i = 0; i < SCAN_PER; ++i) {
+            const long long r = R[k0 + i];
+            mag += (float)(r < 0 ? -r : r);
+            loc += r;
+            s1[i] = loc;
+        }
+        inc1 = wave_incl_scan_i64(loc);
+        mag = wave_sum_f32(mag);
+        if (lane == 63) {
+            sh_s1[w] = inc1;
+            sh_mag[w] = mag;
         }
     }
+    __syncthreads();
+    float mag = 0.0f;
+    long long off1 = 0;
+#pragma unroll
+    for (int q = 0; q < SCAN_WAVES; ++q) {
+        mag += sh_mag[q];
+        if (q < w) off1 += sh_s1[q];
+    }
+    const bool narrow = mag * (float)N < 2305843009213693952.0f;    // 2^61
+    // the thread's nodes' S1 (zero past the last interior node) and their sum
+    long long t64 = 0, inc64 = 0;
+    I128 t128 = i128(0), inc128 = i128(0);
+    if (w < SCAN_WAVES) {
+        off1 += inc1 - loc;
+#pragma unroll
+        for (int i = 0; i < SCAN_PER; ++i) s1[i] = k0 + i < N - 1 ? s1[i] + off1 : 0;
+        if (narrow) {
+#pragma unroll
+            for (int i = 0; i < SCAN_PER; ++i) t64 += s1[i];
+            inc64 = wave_incl_scan_i64(t64);
+            if (lane == 63) sh_t[w] = i128(inc64);
+        } else {
+#pragma unroll
+            for (int i = 0; i < SCAN_PER; ++i) t128 = add(t128, i128(s1[i]));
+            inc128 = wave_incl_scan_i128(t128);
+            if (lane == 63) sh_t[w] = inc128;
+        }
+    }
+    __syncthreads();
     I128 T_N;
-    I128 Tacc = block_scan_excl_i128<SCAN_WAVES>(tl, sh128, T_N);
-    if (j1 > a0 - 1 && j0 <= b0) {
-        long long S1 = s1off;
-        for (int j = j0; j < j1; ++j) {
-            S1 += R[j];
-            if (j >= a0 - 1 && j <= b0) tT[j - a0 + 1] = Tacc;
-            if (j >= 1 && j <= N - 1) Tacc = add(Tacc, i128(S1));
+    // T_j at node j = k + 1 is the sum over the interior nodes before it
+    if (narrow) {
+        long long off = 0, tot = 0;
+#pragma unroll
+        for (int q = 0; q < SCAN_WAVES; ++q) {
+            const long long t = (long long)sh_t[q].lo;
+            if (q < w) off += t;
+            tot += t;
+        }
+        T_N = i128(tot);
+        if (w < SCAN_WAVES && k0 + SCAN_PER >= a0 - 1 && k0 < b0) {
+            long long T_j = off + inc64 - t64;
+#pragma unroll
+            for (int i = 0; i < SCAN_PER; ++i) {
+                const int j = k0 + i + 1;
+                if (j >= a0 - 1 && j <= b0) tT[j - a0 + 1] = i128(T_j);
+                T_j += s1[i];
+            }
+        }
+    } else {
+        I128 off = i128(0);
+        T_N = i128(0);
+#pragma unroll
+        for (int q = 0; q < SCAN_WAVES; ++q) {
+            const I128 t = sh_t[q];
+            if (q < w) off = add(off, t);
+            T_N = add(T_N, t);
+        }
+        if (w < SCAN_WAVES && k0 + SCAN_PER >= a0 - 1 && k0 < b0) {
+            I128 T_j = add(off, add(inc128, neg(t128)));
+#pragma unroll
+            for (int i = 0; i < SCAN_PER; ++i) {
+                const int j = k0 + i + 1;
+                if (j >= a0 - 1 && j <= b0) tT[j - a0 + 1] = T_j;
+                T_j = add(T_j, i128(s1[i]));
+            }
         }
     }
     __syncthreads();
@@ -2519,8 +2612,7 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
     const int tid = threadIdx.x;
     const int j = a0 + tid;                           // this thread's node
 
-    RareTally copy{};
-    if (mode == 0) copy = field_step_reads(dd, fs);
+    if (mode == 0) field_step_reads(dd, fs, role);
     // the launch's epoch and whether the step is averaged (the host sets
     // avg_on between steps), read with the counters at the start
     if (tid == 0) s_epoch = __hip_atomic_load(glb(&st->field_epoch), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2544,7 +2636,7 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
     const uint32_t epoch = s_epoch;
     const int avg = uni(s_avg);
     if (mode == 0) {
-        field_step_plan(dd, parity, step, role, copy, fs, keys);
+        field_step_plan(dd, parity, step, role, fs, keys);
         if (__builtin_expect(records, 0)) {
             // the newborns' records and tallies; the flag releases the
             // tallies to the tail block, which waits for them only when the

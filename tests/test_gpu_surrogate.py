@@ -241,6 +241,29 @@ def test_profile_load_batched(torch, O):
         _check_load(O, cfgs[d], h, *prof[d], d=d)
 
 
+@pytest.mark.parametrize("cells,per_cell,electrons",
+                         [(2, 500, 1.0), (3, 40, 0.0), (5, 40, 0.5), (256, 100, 0.0), (1025, 20, 0.9), (2047, 200, 1.0),
+                          (2048, 60, 0.0), (2048, 300, 0.0), (2047, 400, 0.1)])
+def test_field_of_balanced_and_bare_charge(torch, O, cells, per_cell, electrons):
+    """The exact potential on grids around the scans' four nodes per thread,
+    with charge that 64-bit sums hold and, bare ions of the last two cases
+    (sum of |R| times N above 2^61), charge that needs the 128-bit ones."""
+    from paper_2605_07083_amd import pic
+    cfg = presets.scaled(presets.tiny(), N=cells, n_load=cells * per_cell, gamma_emit=1e21)
+    ne, ni = _profiles(cfg, 5)
+    ne = ne * electrons
+    _say("case: field of %d cells, %d per cell, electrons %.1f" % (cells, per_cell, electrons))
+    h = pic.Handle(cfg, densities=torch.tensor(np.stack([ne, ni])[None], dtype=torch.float64, device="cuda:0"))
+    st, t = gpu_state(h, 0)
+    assert deposit_matches(O, cfg, h, st, 0) == []
+    assert field_matches(O, cfg, h, oracle_from_gpu(O, cfg, st, t), 0) == []
+    assert restart_step_check(O, cfg, h, 2) == []
+    H = [h.hist(0, s) for s in range(3)]
+    wide = float(np.abs((H[2] - H[0] - H[1])[1:-1].astype(float)).sum()) * cells > 2.0 ** 61
+    assert wide == (per_cell >= 300 and electrons < 0.5)
+    h.close()
+
+
 def test_profile_load_errors(torch):
     from paper_2605_07083_amd import pic
     cfg = presets.tiny()
