@@ -236,7 +236,6 @@ void layout(const pic_config *cfgs, int nd, Bump &bp, std::vector<Diode> &hD, Di
         D.E = bp.take<double>(nn);
         D.phi_sum = bp.take<double>(nn);
         D.agg = bp.take<FieldAgg>((nn + FIELD_BIG_TILE - 1) / FIELD_BIG_TILE);     // one per large-grid tile
-        D.agg_flag = bp.take<uint32_t>((nn + FIELD_BIG_TILE - 1) / FIELD_BIG_TILE);
         D.tacc = bp.take<TallyCopy>(TALLY_COPIES);
     }
     zero_end = bp.off;
@@ -1623,7 +1622,7 @@ int pic_load(pic_handle *h, const void *host_buf, size_t bytes)
         }
         s0.arrive = 0;           // no field step is in flight at a step boundary
         s0.spill_flag = 0u;
-        s0.field_epoch = 0u;     // with the tile flags cleared below
+        s0.field_epoch = 0u;     // with the tile aggregates cleared below
         cc += sizeof(DiodeState);
         if ((rc = xfer<false>(cc, D.tally, sizeof(DiodeTally))) || (rc = xfer<false>(cc, D.ring, sizeof(TallySnap) * RING)))
             return rc;
@@ -1650,7 +1649,7 @@ int pic_load(pic_handle *h, const void *host_buf, size_t bytes)
         // per-step scratch starts clear
         for (int s = 0; s < NSP; ++s) HIP_TRY(hipMemset(D.cell_cnt[s], 0, nn * sizeof(int32_t)));
         HIP_TRY(hipMemset(D.tacc, 0, sizeof(TallyCopy) * TALLY_COPIES));
-        HIP_TRY(hipMemset(D.agg_flag, 0, sizeof(uint32_t) * ((nn + FIELD_BIG_TILE - 1) / FIELD_BIG_TILE)));
+        HIP_TRY(hipMemset(D.agg, 0, sizeof(FieldAgg) * ((nn + FIELD_BIG_TILE - 1) / FIELD_BIG_TILE)));
     }
     h->sort_next = true;
     return PIC_OK;

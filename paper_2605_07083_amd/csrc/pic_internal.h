@@ -84,7 +84,7 @@ struct DiodeState {
     int32_t rare_n[NSP];   // rare items (candidates, absorbed) listed this step
     int32_t arrive;        // field step: blocks that have read this step's counters
     uint32_t spill_flag;   // field step: step + 1 once the spilled rare items are done
-    uint32_t field_epoch;  // large-grid field step: launches so far (tile aggregate flags are epoch + 1)
+    uint32_t field_epoch;  // large-grid field step: launches so far (tile aggregates carry epoch + 1)
     // Species s lives in buffer parity ^ flip[s]: a re-sort that keeps a
     // species where it is (keep[s], decided by the re-sort's scan) flips the
     // diode's parity but not the species' buffer, so it toggles flip[s].
@@ -154,15 +154,13 @@ struct alignas(256) TallyCopy {
     RareTally t;
 };
 
-// Per-tile aggregates of the tiled field solve: A = sum of rho over the tile,
-// B (128-bit, lo/hi) = sum over its interior nodes of the in-tile inclusive
-// prefix of rho, n = its interior node count.
+// Per-tile aggregates of the tiled field solve: A = sum of rho over the tile
+// (64 bits), B = sum over its interior nodes of the in-tile inclusive prefix of
+// rho (96 bits: 512 nodes of prefixes below 2^63), 32 bits per word under the
+// epoch of the launch that wrote it.
+constexpr int AGG_WORDS = 5;
 struct FieldAgg {
-    long long A;
-    unsigned long long B_lo;
-    long long B_hi;
-    int32_t n;
-    int32_t pad;
+    unsigned long long w[AGG_WORDS];
 };
 
 // Read-only parameters and buffer pointers of one diode (device copy).
@@ -197,7 +195,6 @@ struct Diode {
     DiodeTally *tally;
     TallySnap *ring;
     FieldAgg *agg;         // the large-grid field step's tile aggregates
-    uint32_t *agg_flag;    // and their flags (field_epoch + 1 once published)
     uint32_t *rare[NSP];   // the step's rare items per species: slot | kind << 30
     TallyCopy *tacc;       // TALLY_COPIES accumulators of the particle kernel's tallies
 };

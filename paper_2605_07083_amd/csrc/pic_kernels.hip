@@ -1893,7 +1893,9 @@ __device__ __forceinline__ I128 wave_incl_scan_i128(I128 x)
 //   k_field_tiles  (larger grids) tiles of BIG_TILE nodes; a tile block
 //                  publishes its aggregates (A_t = sum of its charge, B_t =
 //                  sum over its interior nodes of the in-tile inclusive
-//                  prefix, n_t interior nodes) with a flag and combines the
+//                  prefix), every 32 bits of them beside the launch's epoch in
+//                  a 64-bit word, so that a reader needs no flag and neither
+//                  side a cache write-back or invalidation, and combines the
 //                  aggregates of the tiles before it: P_t = sum_{u<t} A_u is
 //                  S1 before the tile, Q_t = sum_{u<t} (n_u P_u + B_u) is T
 //                  before it.  T_N needs every tile, so the tiles write
@@ -1905,9 +1907,10 @@ __device__ __forceinline__ I128 wave_incl_scan_i128(I128 x)
 // ---------------------------------------------------------------------------
 constexpr int TILE = 512;                 // nodes per tile block of k_field_step
 // Every node's charge staged in each block's LDS.  Above 2049 nodes the tiles'
-// look-back costs less than every block scanning the whole grid (4097 nodes:
-// 60.6 against 62.8 us per step); at 2049 the whole-grid scans still win in
-// batches (32 diodes: 145.8 against 146.9 us per step).
+// look-back costs less than every block scanning the whole grid (when a scan
+// took 3 us, 4097 nodes: 60.6 against 62.8 us per step); at 2049 the whole-grid
+// scans win (one diode 20.0 against 20.8 us per step, 32 diodes 136.3 against
+// 140.4).
 constexpr int FUSED_MAX_NODES = 2049;
 // nodes per tile block of k_field_tiles (one per thread of its first half:
 // the per-node work of a tile runs on one CU, so smaller tiles spread it)
@@ -2287,9 +2290,8 @@ __device__ __forceinline__ void field_step_tail(const Diode &dd, FieldShared &fs
 }
 
 // What a tile's potential and output need of the diode, copied into LDS by
-// one thread at the start of a field block: read later, after the look-back's
-// acquire loads (which invalidate the caches), each of these fields would
-// cost a round trip to memory.
+// one thread at the start of a field block: read where they are used, each of
+// these fields would cost a round trip to memory.
 struct TileConsts {
     double V, alpha, dz;
     int N;
@@ -2565,7 +2567,8 @@ __global__ __launch_bounds__(FT) void k_field_step(const Diode *__restrict__ D, 
     }
     __syncthreads();
     // the own tile's field and potential on the first waves, its node
-    // bookkeeping on the last ones
+    // bookkeeping on the last ones (before the sums instead, on the same waves,
+    // its stores cost the 32-diode batch 0.6 us a step)
     static_assert(FT >= 2 * TILE, "separate waves for the field and the bookkeeping");
     if (tid < TILE) {
         if (a0 + tid < b0) field_node_phi(fc, ph, tid + 1, a0 + tid, avg);
@@ -2612,6 +2615,7 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
     const int tid = threadIdx.x;
     const int j = a0 + tid;                           // this thread's node
 
+    FieldAgg *agg = dd.agg;
     if (mode == 0) field_step_reads(dd, fs, role);
     // the launch's epoch and whether the step is averaged (the host sets
     // avg_on between steps), read with the counters at the start
@@ -2658,6 +2662,12 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
     } else if (tid == 0 && !writer) {
         // done with the epoch: the writer advances it once every tile has read it
         __hip_atomic_fetch_add(glb(&st->arrive), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the node bookkeeping, on waves that the sums leave idle; only this block
+    // reads the tile's H, so it clears it
+    if (tid >= FT - BIG_TILE) {
+        const int i = tid - (FT - BIG_TILE);
+        if (a0 + i < b0) field_node_hist<BIG_TILE>(fc, hb, i, a0 + i, avg, true);
     }
 
     // The tile's aggregates with one barrier: per wave, the inclusive prefix
@@ -2707,37 +2717,35 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
         }
         if (lane == TW - 1) {
             s_B = bi;
-            FieldAgg g;
-            g.A = ai;
-            g.B_lo = bi.lo;
-            g.B_hi = bi.hi;
-            g.n = nint;
-            g.pad = 0;
-            dd.agg[t] = g;
-            // the release store orders the aggregate before the flag
-            __hip_atomic_store(glb(&dd.agg_flag[t]), epoch + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t part[AGG_WORDS] = {(uint32_t)ai, (uint32_t)((unsigned long long)ai >> 32), (uint32_t)bi.lo,
+                                              (uint32_t)(bi.lo >> 32), (uint32_t)bi.hi};
+#pragma unroll
+            for (int k = 0; k < AGG_WORDS; ++k)
+                __hip_atomic_store(glb(&agg[t].w[k]), (unsigned long long)(epoch + 1u) << 32 | part[k], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
         }
-    }
-    if (tid < 64) {
         // the tiles before this one, one lane each: P_u = sum_{v<u} A_v, the
         // sum of S1 over tile u's interior nodes n_u P_u + B_u, and their sums
         const int u = tid;
         long long Au = 0;
         I128 Bu = i128(0);
         int nu = 0;
-        // Relaxed polls, then one acquire fence for the wave: an acquire load
-        // invalidates the XCD's L2 on every poll (instructions included).
         if (u < t) {
-            while (__hip_atomic_load(glb(&dd.agg_flag[u]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch + 1u)
+            unsigned long long g[AGG_WORDS];
+            for (;;) {
+                bool all = true;
+#pragma unroll
+                for (int k = 0; k < AGG_WORDS; ++k) {
+                    g[k] = __hip_atomic_load(glb(&agg[u].w[k]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    all = all && (uint32_t)(g[k] >> 32) == epoch + 1u;
+                }
+                if (all) break;
                 __builtin_amdgcn_s_sleep(1);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        if (u < t) {
-            const FieldAgg g = dd.agg[u];
-            Au = g.A;
-            Bu.lo = g.B_lo;
-            Bu.hi = g.B_hi;
-            nu = g.n;
+            }
+            Au = (long long)((g[0] & 0xFFFFFFFFull) | g[1] << 32);
+            Bu.lo = (g[2] & 0xFFFFFFFFull) | g[3] << 32;
+            Bu.hi = (long long)(int32_t)(uint32_t)g[4];
+            nu = max(0, min((u + 1) * BIG_TILE, N) - max(u * BIG_TILE, 1));
         }
         const long long Pu = wave_incl_scan_i64(Au) - Au;
         const I128 incl = wave_incl_scan_i128(add(mul_small(i128(Pu), (unsigned)nu), Bu));
@@ -2763,16 +2771,7 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
     }
     if (tid == 128 && b0 <= N) ph[b0 - a0 + 1] = phi_prime(fc, b0, add(add(Q, mul_small(i128(P), (unsigned)nint)), B));
     __syncthreads();
-    // the tile's field and potential on its waves, its node bookkeeping on as
-    // many others (after every tile's release, whose L2 write-back would
-    // otherwise take these stores too); only this block reads the tile's H,
-    // so it clears it
-    if (j < b0) {
-        field_node_phi(fc, ph, tid + 1, j, avg);
-    } else if (tid >= FT - BIG_TILE) {
-        const int i = tid - (FT - BIG_TILE);
-        if (a0 + i < b0) field_node_hist<BIG_TILE>(fc, hb, i, a0 + i, avg, true);
-    }
+    if (j < b0) field_node_phi(fc, ph, tid + 1, j, avg);
     if (!writer) return;
     // the writer's tile ends at node N: T_N = Q + n P + B, slope = alpha T_N / N
     if (tid == 0) {
