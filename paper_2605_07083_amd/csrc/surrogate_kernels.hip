@@ -1100,12 +1100,13 @@ constexpr int NET_CUS = 256;
 // blocks; the rows with the least of it are taken.  Measured on the forward
 // pass (2048 cells; 32 / 64 / 128 / 192 rows, us): 1 sample 7.9 / 11.5 / 18 /
 // 22, 8 samples 19 / 15.4 / 20 / 24, 32 samples 63 / 34 / 32 / 33, 64 samples
-// 113 / 60 / 50 / 43.
+// 113 / 60 / 50 / 43.  160 rows give 32 samples two blocks per CU, where 128
+// need three and 192 carry more halo: 28.8 against 31.2 us.
 static int net_rows(int X, int B, int most)
 {
     int rows = 0;
     double best = 0.0;
-    for (int r : {32, 64, 96, 128, 192}) {
+    for (int r : {32, 64, 96, 128, 160, 192}) {
         if (r > most) break;
         const long long blocks = (long long)((X + r - NET_HALO - 1) / (r - NET_HALO)) * B;
         const long long per_cu = (blocks + NET_CUS - 1) / NET_CUS;
@@ -1188,7 +1189,7 @@ extern "C" hipError_t surx_net_train(const __bf16 *const *wf, const float *const
     tr.loss = loss;
     tr.B = B;
     // one channel tile per wave throughout: with two (and 192 rows) the step of
-    // 32 samples x 2048 cells took 164 us, with 128 rows and one 154
+    // 32 samples x 2048 cells took 164 us, with 128 or 160 rows and one 154
     const NetShape n = net_shape(X, B, net_rows(X, B, 128));
     *blocks = (int)n.grid;
     hipLaunchKernelGGL(k_net_train, dim3(n.grid), dim3(NET_THREADS), n.lds, s, net_params(wf, bias), params, tr, X,

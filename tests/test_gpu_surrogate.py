@@ -389,7 +389,7 @@ def test_state_load_over_the_blocks_of_cells(torch, O, cells, per_cell):
     h.close()
 
 
-@pytest.mark.parametrize("B,X", [(1, 64), (2, 128), (9, 320), (20, 704), (70, 64), (5, 4096), (33, 1216), (64, 2048)])
+@pytest.mark.parametrize("B,X", [(1, 64), (2, 128), (9, 320), (20, 704), (70, 64), (5, 4096), (33, 1216), (64, 2048), (32, 2048), (48, 2048)])
 def test_forward_is_the_same_on_every_tiling(sur, torch, B, X):
     """Rows per block follow the batch and the length (32 to 192, the last tile
     ragged); the values do not: a batch equals its samples one at a time, bit
