@@ -2373,7 +2373,7 @@ __global__ __launch_bounds__(FT) void k_field_step(const Diode *__restrict__ D, 
     __shared__ I128 tT[TILE + 2];                     // T_j on the own tile and its halo
     __shared__ FieldShared fs;
     __shared__ TileConsts fc;
-    __shared__ int s_avg, s_last;
+    __shared__ int s_last;
     const Diode &dd = D[blockIdx.y];
     DiodeState *st = dd.st;
     const int N = dd.N, nn = N + 1;
@@ -2404,10 +2404,8 @@ __global__ __launch_bounds__(FT) void k_field_step(const Diode *__restrict__ D, 
         }
     }
     if (mode == 0) field_step_reads(dd, fs, role);
+    else if (tid >= 64 && tid < 128) load_state(st, &fs.s_st);
     if (tid == 128) tile_consts(dd, fc);
-    // whether the step is averaged (the host sets avg_on between steps)
-    if (tid == 1) s_avg = __hip_atomic_load(glb(&st->avg_on), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t step = mode == 0 ? (uint32_t)uni((int)st->step) : 0u;
     if (tile) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -2424,7 +2422,10 @@ __global__ __launch_bounds__(FT) void k_field_step(const Diode *__restrict__ D, 
         }
     }
     __syncthreads();
-    const int avg = uni(s_avg);
+    // the step, and whether it is averaged (the host sets avg_on between steps),
+    // from the counters: loads of their own were one more trip to memory
+    const uint32_t step = mode == 0 ? (uint32_t)uni((int)fs.s_st.step) : 0u;
+    const int avg = uni(fs.s_st.avg_on);
     if (mode == 0) {
         field_step_plan(dd, parity, step, role, fs, keys);
         if (__builtin_expect(records, 0)) {
@@ -2599,8 +2600,6 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
     __shared__ I128 s_Q, s_B;                         // S1, T before the tile; the tile's B
     __shared__ long long s_Pw[BIG_TILE / 64];         // per wave of the tile: charge of the earlier waves,
     __shared__ I128 s_Qw[BIG_TILE / 64];              //   their sum of S1 over interior nodes
-    __shared__ uint32_t s_epoch;
-    __shared__ int s_avg;
     __shared__ TileConsts fc;
     const Diode &dd = D[blockIdx.y];
     DiodeState *st = dd.st;
@@ -2616,29 +2615,28 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
     const int j = a0 + tid;                           // this thread's node
 
     FieldAgg *agg = dd.agg;
-    if (mode == 0) field_step_reads(dd, fs, role);
-    // the launch's epoch and whether the step is averaged (the host sets
-    // avg_on between steps), read with the counters at the start
-    if (tid == 0) s_epoch = __hip_atomic_load(glb(&st->field_epoch), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid == 1) s_avg = __hip_atomic_load(glb(&st->avg_on), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid == 128) tile_consts(dd, fc);
-    if (tile) {
-        long long r = 0;
-        if (j < b0) {
-            unsigned long long h[NSP];
+    // the tile's deposits, requested before the counters' and tallies' waves wait for theirs
+    unsigned long long h[NSP];
+    if (tile && tid < BIG_TILE) {
 #pragma unroll
-            for (int s = 0; s < NSP; ++s) {
-                h[s] = glb(dd.H[s])[j];
-                hb[s][tid] = h[s];
-            }
-            if (j >= 1 && j <= N - 1) r = (long long)(h[SP_I] - h[SP_P] - h[SP_E]);
-        }
-        if (tid < BIG_TILE) R[tid] = r;
+        for (int s = 0; s < NSP; ++s) h[s] = glb(dd.H[s])[min(j, N)];
     }
-    const uint32_t step = mode == 0 ? (uint32_t)uni((int)st->step) : 0u;
+    if (mode == 0) field_step_reads(dd, fs, role);
+    else if (tid >= 64 && tid < 128) load_state(st, &fs.s_st);
+    if (tid == 128) tile_consts(dd, fc);
+    if (tile && tid < BIG_TILE) {
+        R[tid] = j >= 1 && j <= N - 1 ? (long long)(h[SP_I] - h[SP_P] - h[SP_E]) : 0;
+        if (j < b0) {
+#pragma unroll
+            for (int s = 0; s < NSP; ++s) hb[s][tid] = h[s];
+        }
+    }
     __syncthreads();
-    const uint32_t epoch = s_epoch;
-    const int avg = uni(s_avg);
+    // from the counters: the step, the launch's epoch and whether the step is
+    // averaged (the host sets avg_on between steps)
+    const uint32_t step = mode == 0 ? (uint32_t)uni((int)fs.s_st.step) : 0u;
+    const uint32_t epoch = fs.s_st.field_epoch;
+    const int avg = uni(fs.s_st.avg_on);
     if (mode == 0) {
         field_step_plan(dd, parity, step, role, fs, keys);
         if (__builtin_expect(records, 0)) {
