@@ -602,18 +602,19 @@ int refield(pic_handle *h, bool sorted)
 template <class Launch>
 int read_back(pic_handle *h, Launch launch)
 {
-    if (!h->read) {
+    if (h->device < 0) {
         hipPointerAttribute_t a{};
         HIP_TRY(hipPointerGetAttributes(&a, h->ws));
-        void *p = nullptr;
-        HIP_TRY(hipHostMalloc(&p, sizeof(ReadBack) + 3 * sizeof(double) * h->max_nodes, hipHostMallocDefault));
-        h->read = static_cast<ReadBack *>(p);
         h->device = a.device;
     }
     int dev = h->device;
     HIP_TRY(hipGetDevice(&dev));
     if (dev != h->device) HIP_TRY(hipSetDevice(h->device));
-    const hipError_t e = launch();
+    hipError_t e = hipSuccess;
+    if (!h->read)
+        e = hipHostMalloc(reinterpret_cast<void **>(&h->read),
+                          sizeof(ReadBack) + 3 * sizeof(double) * h->max_nodes, hipHostMallocDefault);
+    if (e == hipSuccess) e = launch();
     if (dev != h->device) (void)hipSetDevice(dev);
     HIP_TRY(e);
     HIP_TRY(hipStreamSynchronize(h->stream));
