@@ -155,7 +155,12 @@ int pic_workspace_size(const pic_config *cfgs, int n_diodes, size_t *bytes);
  * pic_workspace_size bytes (256-byte aligned), bound to hip_stream (a
  * hipStream_t; NULL = default stream).  Enqueues the initial load (uniform
  * positions, Maxwellian velocities; "Model"), the first deposit and the first
- * field solve.  Asynchronous. */
+ * field solve.  Asynchronous.  The handle also borrows a block of pinned host
+ * memory that its reads of tallies and profiles go through (512 bytes + 24
+ * per node, rounded up to a power of two): no read allocates, and closing a
+ * handle waits for no stream.  The library keeps up to 64 such blocks, 8 MiB
+ * in all, for the handles to come; only a block beyond that is freed, for
+ * which the runtime waits for the GPU's work. */
 int pic_init(const pic_config *cfgs, int n_diodes, void *dev_workspace, size_t bytes,
              void *hip_stream, pic_handle **out);
 

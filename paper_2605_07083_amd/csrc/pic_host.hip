@@ -313,6 +313,71 @@ struct GraphEntry {
     uint64_t last_use = 0;
 };
 
+// Pinned host blocks for the read-back kernels, lent to handles.  hipHostFree
+// waits for all work of the GPU, whichever stream it is on, so a block that
+// went with its handle made closing one wait for the others (30 ms beside a
+// stream with that much work, 2 us with the block put back), and a program that
+// creates, reads and closes paid an allocation each time (50 us).  The pool
+// keeps up to MAX_BLOCKS free blocks and MAX_BYTES in them for the handles to
+// come and frees what is put back beyond that.  Never destroyed: handles may be
+// closed while the process ends.
+class PinnedPool {
+public:
+    struct Block {
+        void *p = nullptr;
+        size_t bytes = 0;
+        int device = -1;      // the GPU that was current when it was allocated
+    };
+    static PinnedPool &instance()
+    {
+        static PinnedPool *pool = new PinnedPool;
+        return *pool;
+    }
+    // A block of at least `bytes` for the current GPU `device`.
+    hipError_t get(size_t bytes, int device, Block &out)
+    {
+        size_t size = 4096;    // powers of two, so that handles of like sizes share blocks
+        while (size < bytes) size *= 2;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            for (int k = 0; k < count; ++k)
+                if (blocks[k].bytes == size && blocks[k].device == device) {
+                    out = blocks[k];
+                    blocks[k] = blocks[--count];
+                    held -= size;
+                    return hipSuccess;
+                }
+        }
+        hipError_t e = hipHostMalloc(&out.p, size, hipHostMallocDefault);
+        if (e != hipSuccess) return e;
+        out.bytes = size;
+        out.device = device;
+        return hipSuccess;
+    }
+    // Takes a block back that no kernel writes any more.
+    void put(const Block &b)
+    {
+        if (!b.p) return;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            if (count < MAX_BLOCKS && held + b.bytes <= MAX_BYTES) {
+                blocks[count++] = b;
+                held += b.bytes;
+                return;
+            }
+        }
+        (void)hipHostFree(b.p);
+    }
+
+private:
+    static constexpr int MAX_BLOCKS = 64;
+    static constexpr size_t MAX_BYTES = (size_t)8 << 20;
+    std::mutex mu;
+    Block blocks[MAX_BLOCKS];
+    int count = 0;
+    size_t held = 0;
+};
+
 struct pic_handle {
     int nd = 0;
     std::vector<pic_config> cfg;
@@ -340,10 +405,11 @@ struct pic_handle {
     std::vector<hipEvent_t> evpool;         // pic_step_timed's events, created on demand, reused
     hipEvent_t tev[2] = {nullptr, nullptr}; // placeholders for event nodes not timed in a replay
     hipEvent_t tt[2] = {nullptr, nullptr};  // start and end of a timed run
-    // pinned host memory of the read-back kernels, of the first read; the
-    // mutex lets several threads read one handle
+    // pinned host memory of the read-back kernels, from creation on; the mutex
+    // lets several threads read one handle
     std::mutex read_mu;
-    ReadBack *read = nullptr;
+    PinnedPool::Block read;
+    bool read_lost = false;                 // a read ended in an error: its kernel may still write
     int device = -1;                        // the workspace's GPU
     void drop_graphs()
     {
@@ -362,7 +428,7 @@ struct pic_handle {
         for (auto e : tt)
             if (e) (void)hipEventDestroy(e);
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
-        if (read) (void)hipHostFree(read);
+        if (!read_lost) PinnedPool::instance().put(read);
     }
     std::vector<std::array<int64_t, NSP>> live_offset;
 };
@@ -597,37 +663,59 @@ int refield(pic_handle *h, bool sorted)
     return PIC_OK;
 }
 
-// Runs a read-back kernel on the handle's stream, with its GPU current, and
-// waits for it; the caller holds read_mu.
-template <class Launch>
-int read_back(pic_handle *h, Launch launch)
+// Runs f with the handle's GPU current.
+template <class F>
+hipError_t on_device(const pic_handle *h, F f)
 {
-    if (h->device < 0) {
-        hipPointerAttribute_t a{};
-        HIP_TRY(hipPointerGetAttributes(&a, h->ws));
-        h->device = a.device;
-    }
     int dev = h->device;
-    HIP_TRY(hipGetDevice(&dev));
-    if (dev != h->device) HIP_TRY(hipSetDevice(h->device));
-    hipError_t e = hipSuccess;
-    if (!h->read)
-        e = hipHostMalloc(reinterpret_cast<void **>(&h->read),
-                          sizeof(ReadBack) + 3 * sizeof(double) * h->max_nodes, hipHostMallocDefault);
-    if (e == hipSuccess) e = launch();
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev != h->device && (e = hipSetDevice(h->device)) != hipSuccess) return e;
+    e = f();
     if (dev != h->device) (void)hipSetDevice(dev);
+    return e;
+}
+
+// The GPU of the workspace (the current one where the runtime does not know the
+// memory) and the handle's pinned block.
+int prepare_reads(pic_handle *h)
+{
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, h->ws) == hipSuccess && a.type == hipMemoryTypeDevice) {
+        h->device = a.device;
+    } else {
+        (void)hipGetLastError();
+        HIP_TRY(hipGetDevice(&h->device));
+    }
+    const size_t bytes = sizeof(ReadBack) + 3 * sizeof(double) * h->max_nodes;
+    const hipError_t e = on_device(h, [&] { return PinnedPool::instance().get(bytes, h->device, h->read); });
+    if (e != hipSuccess) return fail(PIC_EHIP, std::string("pinned memory of the reads: ") + hipGetErrorString(e));
+    return PIC_OK;
+}
+
+// Runs a read-back kernel on the handle's stream and waits for it; the caller
+// holds read_mu.
+template <class Launch>
+int read_back(pic_handle *h, Launch launch, const ReadBack *&out)
+{
+    ReadBack *r = static_cast<ReadBack *>(h->read.p);
+    out = r;
+    hipError_t e = on_device(h, [&] { return launch(r); });
+    if (e != hipSuccess) return fail(PIC_EHIP, std::string("read-back launch: ") + hipGetErrorString(e));
+    e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) h->read_lost = true;
     HIP_TRY(e);
-    HIP_TRY(hipStreamSynchronize(h->stream));
     return PIC_OK;
 }
 
 int read_state(pic_handle *h, int d, DiodeState &st, DiodeTally &t)
 {
     std::lock_guard<std::mutex> lock(h->read_mu);
-    int rc = read_back(h, [&] { return picx_launch_read_tally(h->dD, d, h->read, h->stream); });
+    const ReadBack *r;
+    int rc = read_back(h, [&](ReadBack *out) { return picx_launch_read_tally(h->dD, d, out, h->stream); }, r);
     if (rc) return rc;
-    st = h->read->st;
-    t = h->read->tally;
+    st = r->st;
+    t = r->tally;
     return PIC_OK;
 }
 
@@ -758,6 +846,7 @@ static int init_impl(const pic_config *cfgs, int n_diodes, void *dev_workspace, 
 
     auto cleanup = [&](int code) { delete h; return code; };
     if (picx_prepare() != hipSuccess) return cleanup(fail(PIC_EHIP, "kernel attribute setup failed"));
+    if ((rc = prepare_reads(h))) return cleanup(rc);
     size_t zbeg = (reinterpret_cast<char *>(h->hD[0].st) - h->ws);
     if (hipMemsetAsync(h->ws + zbeg, 0, zend - zbeg, h->stream) != hipSuccess)
         return cleanup(fail(PIC_EHIP, "hipMemsetAsync failed"));
@@ -973,10 +1062,12 @@ int pic_get_fields(pic_handle *h, int diode, double *phi, double *n_e, double *n
     if (!h || diode < 0 || diode >= h->nd) return fail(PIC_EINVAL, "bad arguments");
     const int nn = h->cfg[diode].N + 1;
     std::lock_guard<std::mutex> lock(h->read_mu);
-    int rc = read_back(h, [&] { return picx_launch_read_fields(h->dD, diode, nn, time_avg, h->read, h->stream); });
+    const ReadBack *r;
+    int rc = read_back(
+        h, [&](ReadBack *out) { return picx_launch_read_fields(h->dD, diode, nn, time_avg, out, h->stream); }, r);
     if (rc) return rc;
-    if (time_avg && h->read->st.avg_steps == 0) return fail(PIC_EINVAL, "no time average accumulated");
-    const double *v = reinterpret_cast<const double *>(h->read + 1);
+    if (time_avg && r->st.avg_steps == 0) return fail(PIC_EINVAL, "no time average accumulated");
+    const double *v = reinterpret_cast<const double *>(r + 1);
     for (double *out : {phi, n_e, n_i}) {
         if (out) std::memcpy(out, v, nn * sizeof(double));
         v += nn;

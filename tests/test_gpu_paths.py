@@ -454,3 +454,53 @@ def test_read_back_of_profiles_and_tallies(pic, cells):
         assert all(np.array_equal(t[q], want[0][d][q]) for q in t)
         assert all(np.array_equal(f[q], want[1][d][q]) for q in f)
     h.close()
+
+
+def test_closing_a_handle_waits_for_no_other_stream(pic):
+    """Creating, reading and closing a handle leaves the work of other streams
+    running: a queue of at least 20 ms beside it is not at its end when the
+    handle is gone."""
+    import torch
+    a = torch.randn(8192, 8192, device="cuda:0", dtype=torch.bfloat16)
+    other, mine, done = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Event()
+    with torch.cuda.stream(mine):
+        pic.Handle(presets.tiny()).close()           # first use: code and memory are loaded
+        with torch.cuda.stream(other):
+            for _ in range(20):
+                a @ a
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        for _ in range(400):
+            a @ a
+        done.record()
+    with torch.cuda.stream(mine):
+        h = pic.Handle(presets.tiny())
+        h.step(3)
+        step, phi = h.tally(0)["step"], h.fields(0)["phi"]
+        h.close()
+    running = not done.query()
+    torch.cuda.synchronize()
+    assert running and step == 3 and np.isfinite(phi).all()
+
+
+def test_read_memory_passes_from_handle_to_handle(pic):
+    """Handles of several sizes created, read and closed by several threads at
+    once read what a handle of their own reads alone."""
+    import torch
+    from concurrent.futures import ThreadPoolExecutor
+    cfgs = [presets.scaled(presets.tiny(), N=n, n_load=40 * n, seed=presets.tiny()["seed"] + n)
+            for n in (60, 256, 700, 2600)]
+
+    def one(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            h = pic.Handle(cfgs[i % 4])
+            h.step(4)
+            got = h.tally(0), h.fields(0)
+            h.close()
+        return i % 4, got
+
+    want = dict(one(i) for i in range(4))
+    with ThreadPoolExecutor(6) as ex:
+        for k, (t, f) in ex.map(one, range(48)):
+            assert all(np.array_equal(f[q], want[k][1][q]) for q in f)
+            assert all(np.array_equal(t[q], want[k][0][q]) for q in t if q != "abs_energy")
