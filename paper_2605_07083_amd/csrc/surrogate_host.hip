@@ -23,7 +23,7 @@ hipError_t surx_net_train(const __bf16 *const *wf, const float *const *bias, con
 hipError_t surx_conv_bwd(int layer, const __bf16 *dz, const float *yin, const __bf16 *feat, const __bf16 *Wb,
                          __bf16 *dzprev, float *part, float *pbias, int X, int B, hipStream_t s);
 int surx_wgrad_parts(int X, int B);
-hipError_t surx_reduce_adam(const float *const *part, const float *const *pbias, int P, float *const *wm,
+hipError_t surx_reduce_adam(int layers, const float *const *part, const float *const *pbias, int P, float *const *wm,
                             float *const *mw, float *const *vw, float *const *dw, float *const *bias,
                             float *const *mb, float *const *vb, float *const *db, __bf16 *const *Wf,
                             __bf16 *const *Wb, const int *cin, const int *coutp, const int *cout_real, const int *kp,
@@ -97,6 +97,7 @@ struct sur_net {
     __bf16 *dz[2];                // output gradients of a layer [bmax][X][64], ping-pong
     float *part[SUR_LAYERS];      // partial weight gradients [parts][coutp][kp]
     float *pbias[SUR_LAYERS];     // and bias gradients [parts][coutp]
+    bool reduce_after[SUR_LAYERS];   // whether they are summed once this layer's are written (layout)
     double *loss = nullptr;       // the training loss
     double *loss_parts = nullptr; // its shares per forward block
     long long t = 0;              // Adam steps taken
@@ -130,40 +131,43 @@ void layout(sur_net &n, Bump &bp)
     n.param_bytes = bp.off;
     n.feat = bp.take<__bf16>(P * SUR_IN);
     for (int k = 0; k < 2; ++k) n.dz[k] = bp.take<__bf16>(P * SUR_HIDDEN);
-    // One region for the hidden outputs and the partial gradients.  The
-    // backward pass goes from the last layer to the first and layer l reads
-    // y[l-1] only, so the partials are laid out in that order from the
-    // region's start and the outputs, last layer first, `fresh` bytes in: the
-    // partials of layer l may end where y[l-1] begins.  Grids of whole
-    // 256-position slices need 500 bytes per position before y[4], short
-    // samples more; the region is never below 832 bytes per position and the
-    // largest layer's partials, a size that callers may have planned with.
+    // One region for the forward blocks' shares of the loss, the partial
+    // gradients and the hidden outputs.  The backward pass goes from the last
+    // layer to the first and layer l reads y[l-1] only, so the partials are laid
+    // out in that order behind the shares and the outputs, last layer first, at
+    // the region's end: the partials of layer l may end where y[l-1] begins.
+    // The region is 832 bytes per position and the largest layer's partials
+    // besides the outputs, the size that callers have planned with.  Samples of
+    // whole 256-position slices hold every layer's partials in it; with samples
+    // of 64, 128 or 320 positions the gradients of the layers so far are summed
+    // when it is full (reduce_after) and the next layer starts over.
     const size_t parts = (size_t)surx_wgrad_parts(n.X, n.bmax);
     const size_t ybytes = align_up(P * SUR_HIDDEN * sizeof(float));
-    size_t wbytes[SUR_LAYERS], bbytes[SUR_LAYERS], end = 0, fresh = 0, largest = 0;
-    for (int l = SUR_LAYERS - 1; l >= 0; --l) {
-        wbytes[l] = align_up(parts * n.L[l].coutp * n.L[l].kp * sizeof(float));
-        bbytes[l] = align_up(parts * n.L[l].coutp * sizeof(float));
-        end += wbytes[l] + bbytes[l];
-        largest = std::max(largest, wbytes[l] + bbytes[l]);
-        const size_t dead = (size_t)(SUR_LAYERS - 1 - std::max(l, 1)) * ybytes;   // y[4] .. y[l]
-        if (l > 0 && end > dead) fresh = std::max(fresh, end - dead);
-    }
-    const size_t region = std::max({fresh + (SUR_LAYERS - 1) * ybytes, end,
-                                    align_up(P * 832) + largest + (SUR_LAYERS - 1) * ybytes});
-    fresh = region - (SUR_LAYERS - 1) * ybytes;
+    const size_t largest = parts * (SUR_HIDDEN * pad32(SUR_KS * SUR_HIDDEN) + SUR_HIDDEN) * sizeof(float);
+    const size_t fresh = align_up(P * 832) + align_up(largest), region = fresh + (SUR_LAYERS - 1) * ybytes;
+    const size_t shares = align_up((size_t)surx_net_train_blocks(n.X, n.bmax) * sizeof(double));   // < 832 P
     char *r = bp.take<char>(region);
-    if (r) {
-        size_t off = 0;
-        for (int l = SUR_LAYERS - 1; l >= 0; --l) {
-            n.part[l] = reinterpret_cast<float *>(r + off);
-            n.pbias[l] = reinterpret_cast<float *>(r + off + wbytes[l]);
-            off += wbytes[l] + bbytes[l];
+    size_t off = shares;
+    for (int l = SUR_LAYERS - 1; l >= 0; --l) {
+        const size_t w = align_up(parts * n.L[l].coutp * n.L[l].kp * sizeof(float));
+        const size_t b = align_up(parts * n.L[l].coutp * sizeof(float));
+        const size_t limit = l > 0 ? fresh + (size_t)(SUR_LAYERS - 1 - l) * ybytes : region;
+        n.reduce_after[l] = l == 0;
+        if (off + w + b > limit) {
+            n.reduce_after[l + 1] = true;
+            off = shares;
         }
-        for (int l = 0; l < SUR_LAYERS - 1; ++l)
-            n.y[l] = reinterpret_cast<float *>(r + fresh + (SUR_LAYERS - 2 - l) * ybytes);
+        if (r) {
+            n.part[l] = reinterpret_cast<float *>(r + off);
+            n.pbias[l] = reinterpret_cast<float *>(r + off + w);
+        }
+        off += w + b;
     }
-    n.loss_parts = bp.take<double>((size_t)surx_net_train_blocks(n.X, n.bmax));
+    if (r) {
+        n.loss_parts = reinterpret_cast<double *>(r);
+        for (int l = 0; l < SUR_LAYERS - 1; ++l)
+            n.y[l] = reinterpret_cast<float *>(r + fresh + (size_t)(SUR_LAYERS - 2 - l) * ybytes);
+    }
 }
 
 int check_shape(int batch, int cells)
@@ -358,20 +362,6 @@ int sur_train_step(sur_net *n, const float *dev_params, const float *dev_target,
     n->t += 1;
     const float c1 = (float)(1.0 - std::pow((double)B1, (double)n->t));
     const float c2 = (float)(1.0 - std::pow((double)B2, (double)n->t));
-    // per layer, last to first: the input gradient and the partial weight
-    // gradients in one kernel; then every layer's gradient summed from the
-    // partials, its Adam update and BF16 copies in one launch
-    int cur = 0;
-    for (int l = SUR_LAYERS - 1; l >= 0; --l) {
-        const Layer &L = n->L[l];
-        if (l > 0)
-            SUR_TRY(surx_conv_bwd(l, n->dz[cur], n->y[l - 1], nullptr, L.wb, n->dz[cur ^ 1], n->part[l], n->pbias[l],
-                                  X, batch, n->stream));
-        else
-            SUR_TRY(surx_conv_bwd(0, n->dz[cur], nullptr, n->feat, nullptr, nullptr, n->part[0], n->pbias[0], X,
-                                  batch, n->stream));
-        cur ^= 1;
-    }
     float *wm[SUR_LAYERS], *mw[SUR_LAYERS], *vw[SUR_LAYERS], *dw[SUR_LAYERS];
     float *bm[SUR_LAYERS], *mb[SUR_LAYERS], *vb[SUR_LAYERS], *db[SUR_LAYERS];
     __bf16 *lwf[SUR_LAYERS], *lwb[SUR_LAYERS];
@@ -383,9 +373,28 @@ int sur_train_step(sur_net *n, const float *dev_params, const float *dev_target,
         lwf[l] = L.wf; lwb[l] = L.wb;
         kp[l] = L.kp; kpb[l] = L.kpb;
     }
-    SUR_TRY(surx_reduce_adam(n->part, n->pbias, surx_wgrad_parts(X, batch), wm, mw, vw, dw, bm, mb, vb, db, lwf, lwb,
-                             CIN, COUTP, COUT, kp, kpb, n->loss_parts, shares, n->loss, lr,
-                             B1, B2, EPS, c1, c2, n->stream));
+    // per layer, last to first: the input gradient (with this layer's weights
+    // before their update) and the partial weight gradients in one kernel; once
+    // the region is full or the first layer's are written, the layers' gradients
+    // summed from the partials, their Adam update and BF16 copies in one launch,
+    // the last of them with the loss
+    int cur = 0, top = SUR_LAYERS - 1;
+    for (int l = SUR_LAYERS - 1; l >= 0; --l) {
+        const Layer &L = n->L[l];
+        if (l > 0)
+            SUR_TRY(surx_conv_bwd(l, n->dz[cur], n->y[l - 1], nullptr, L.wb, n->dz[cur ^ 1], n->part[l], n->pbias[l],
+                                  X, batch, n->stream));
+        else
+            SUR_TRY(surx_conv_bwd(0, n->dz[cur], nullptr, n->feat, nullptr, nullptr, n->part[0], n->pbias[0], X,
+                                  batch, n->stream));
+        cur ^= 1;
+        if (!n->reduce_after[l]) continue;
+        SUR_TRY(surx_reduce_adam(top - l + 1, n->part + l, n->pbias + l, surx_wgrad_parts(X, batch), wm + l, mw + l,
+                                 vw + l, dw + l, bm + l, mb + l, vb + l, db + l, lwf + l, lwb + l, CIN + l, COUTP + l,
+                                 COUT + l, kp + l, kpb + l, n->loss_parts, shares, l == 0 ? n->loss : nullptr, lr, B1,
+                                 B2, EPS, c1, c2, n->stream));
+        top = l - 1;
+    }
     if (loss) {
         SUR_TRY(hipMemcpyAsync(loss, n->loss, sizeof(double), hipMemcpyDeviceToHost, n->stream));
         SUR_TRY(hipStreamSynchronize(n->stream));

@@ -19,6 +19,7 @@
 // MFMA 16x16x32 (bf16) lane layout: lane l supplies A[l%16][8(l/16)+i] and
 // B[8(l/16)+i][l%16], i = 0..7, and receives D[4(l/16)+i][l%16], i = 0..3.
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
 #include <type_traits>
 
@@ -467,9 +468,10 @@ __global__ __launch_bounds__(BW_THREADS) void k_conv_bwd(const __bf16 *__restric
 // fragment order and transposed Wb[ci][t*COUTP + co].  A block takes 64
 // consecutive entries of a layer's padded weights [COUTP][KP] followed by its
 // biases; wave w sums the partials w, w + 16, ... of each, and the first wave
-// adds the 16 sums in wave order and updates.  One launch for all layers (6 x
-// 5.5 us as a launch per layer, whose few hundred blocks each left the chip
-// half empty).  One more block adds the loss from the forward blocks' shares.
+// adds the 16 sums in wave order and updates.  One launch for all layers whose
+// partials the workspace holds at once (6 x 5.5 us as a launch per layer, whose
+// few hundred blocks each left the chip half empty).  In the last one, one more
+// block adds the loss from the forward blocks' shares.
 // ---------------------------------------------------------------------------
 constexpr int RA_WAVES = 16;
 
@@ -478,11 +480,11 @@ struct AdamLayer {
     float *wm, *mw, *vw, *dw, *bias, *mb, *vb, *db;
     __bf16 *Wf, *Wb;
     int cin, coutp, cout_real, kp, kpb;
-    int first;               // the layer's first block
+    int first;               // the layer's first block (INT_MAX: none)
 };
 
 struct AdamArgs {
-    AdamLayer L[6];
+    AdamLayer L[6];          // the launch's layers, in front
     int P;                   // partials per layer
     int blocks;              // of all layers
     const double *loss_parts;
@@ -1042,9 +1044,9 @@ extern "C" hipError_t surx_conv_bwd(int layer, const __bf16 *dz, const float *yi
 
 extern "C" int surx_wgrad_parts(int X, int B) { return B * ((X + BW_SLICE - 1) / BW_SLICE); }
 
-// Adam over every layer (the fields of AdamLayer but `first`, per layer) and
-// the loss from the forward blocks' shares.
-extern "C" hipError_t surx_reduce_adam(const float *const *part, const float *const *pbias, int P, float *const *wm,
+// Adam over `layers` layers (the fields of AdamLayer but `first`, per layer)
+// and, where a place for it is given, the loss from the forward blocks' shares.
+extern "C" hipError_t surx_reduce_adam(int layers, const float *const *part, const float *const *pbias, int P, float *const *wm,
                                        float *const *mw, float *const *vw, float *const *dw, float *const *bias,
                                        float *const *mb, float *const *vb, float *const *db, __bf16 *const *Wf,
                                        __bf16 *const *Wb, const int *cin, const int *coutp, const int *cout_real,
@@ -1054,7 +1056,8 @@ extern "C" hipError_t surx_reduce_adam(const float *const *part, const float *co
 {
     AdamArgs A;
     int blocks = 0;
-    for (int l = 0; l < 6; ++l) {
+    for (AdamLayer &L : A.L) L.first = INT_MAX;
+    for (int l = 0; l < layers; ++l) {
         A.L[l] = AdamLayer{part[l], pbias[l], wm[l], mw[l], vw[l], dw[l], bias[l], mb[l], vb[l], db[l], Wf[l], Wb[l],
                            cin[l], coutp[l], cout_real[l], kp[l], kpb[l], blocks};
         blocks += (coutp[l] * kp[l] + coutp[l] + 63) / 64;
@@ -1070,7 +1073,7 @@ extern "C" hipError_t surx_reduce_adam(const float *const *part, const float *co
     A.eps = eps;
     A.c1 = c1;
     A.c2 = c2;
-    hipLaunchKernelGGL(k_reduce_adam, dim3(blocks + 1), dim3(RA_WAVES * 64), 0, s, A);
+    hipLaunchKernelGGL(k_reduce_adam, dim3(blocks + (loss ? 1 : 0)), dim3(RA_WAVES * 64), 0, s, A);
     return hipGetLastError();
 }
 

@@ -137,3 +137,14 @@ def test_steady_state_criterion():
     br2 = np.array([50, 30, 20, 20.2, 20.1])
     r = pic.steady_from_series(br2, np.ones(5), 1.0, 0.01)
     assert r["steady_block"] == 4 and r["blocks_averaged"] == 0
+
+
+# The bytes that the library has asked for at these shapes: (batch, cells), bytes
+@pytest.mark.parametrize("batch,cells,planned",
+                         [(1, 64, 2310912), (64, 64, 17164800), (4096, 64, 967813632), (3, 128, 3243264),
+                          (1000, 128, 391451136), (8, 192, 6418944), (2, 256, 3468288), (64, 320, 61745664),
+                          (8, 448, 11991552), (1, 2048, 7647744), (64, 2048, 358722048), (1, 65536, 180398592)])
+def test_surrogate_workspace_fits_what_callers_planned(batch, cells, planned):
+    """A workspace that was once large enough for a handle still is."""
+    from paper_2605_07083_amd import surrogate
+    assert surrogate.workspace_size(batch, cells) <= planned

@@ -454,3 +454,33 @@ def test_train_step_on_every_tiling(sur, torch, B, X):
     assert abs(loss - np.mean(losses)) <= 1e-12 * loss
     for s, g in zip(sw + sb, gw + gb):
         assert _rel(g, s) <= 1e-5
+
+
+@pytest.mark.parametrize("B,X", [(1, 64), (6, 64), (3, 128), (5, 320), (2, 576), (3, 1024)])
+def test_training_within_its_workspace(sur, torch, B, X):
+    """Samples of 64, 128 and 320 positions sum their gradients in several
+    launches, others in one.  Either way a step writes nothing beyond its
+    workspace, and a batch below the handle's largest gives the same loss,
+    weights and gradients, bit for bit, as a handle of exactly that batch."""
+    import ctypes as C
+    _say("case: training workspace B=%d X=%d" % (B, X))
+    W, b = presets.surrogate_test_weights(41)
+    p = torch.tensor(_params(B, 43), dtype=torch.float32, device="cuda:0")
+    u = np.linspace(0.5 / X, 1 - 0.5 / X, X)
+    t = torch.tensor(np.stack([_target39(u, k) for k in range(B)]), dtype=torch.float32, device="cuda:0")
+    got = []
+    for most in (B, B + 3):
+        n = sur.workspace_size(most, X)
+        net = sur.Surrogate(1, 64, device="cuda:0")
+        net.close()
+        net.ws = torch.full((n + 65536,), 0xA5, dtype=torch.uint8, device="cuda:0")
+        net.max_batch, net.cells, net.h = most, X, C.c_void_p()
+        assert sur.lib().sur_create(most, X, C.c_void_p(net.ws.data_ptr()), n,
+                                    C.c_void_p(net.stream.cuda_stream), 0, C.byref(net.h)) == 0
+        net.set_weights(W, b)
+        losses = [net.train_step(p, t, 1e-3) for _ in range(3)]
+        got.append((losses, [x for v in net.weights() + net.grads() for x in v]))
+        assert bool((net.ws[n:] == 0xA5).all())
+        net.close()
+    assert got[0][0] == got[1][0]
+    assert all(np.array_equal(x, y) for x, y in zip(got[0][1], got[1][1]))
