@@ -66,7 +66,7 @@ struct SpeciesBuf {
     ColdRec *cold;      // v_x, v_y, id
 };
 
-// Nodes per tile of the large-grid field kernel (one aggregate and flag each).
+// Nodes per tile of the large-grid field kernel (one aggregate each).
 constexpr int FIELD_BIG_TILE = 512;
 
 // Mutable per-diode state (device).
@@ -84,7 +84,7 @@ struct DiodeState {
     int32_t rare_n[NSP];   // rare items (candidates, absorbed) listed this step
     int32_t arrive;        // field step: blocks that have read this step's counters
     uint32_t spill_flag;   // field step: step + 1 once the spilled rare items are done
-    uint32_t field_epoch;  // large-grid field step: launches so far (tile aggregates carry epoch + 1)
+    uint32_t field_epoch;  // large-grid field step: launches so far (tile aggregates carry the low bits of epoch + 1)
     // Species s lives in buffer parity ^ flip[s]: a re-sort that keeps a
     // species where it is (keep[s], decided by the re-sort's scan) flips the
     // diode's parity but not the species' buffer, so it toggles flip[s].
@@ -156,12 +156,33 @@ struct alignas(256) TallyCopy {
 
 // Per-tile aggregates of the tiled field solve: A = sum of rho over the tile
 // (64 bits), B = sum over its interior nodes of the in-tile inclusive prefix of
-// rho (96 bits: 512 nodes of prefixes below 2^63), 32 bits per word under the
-// epoch of the launch that wrote it.
-constexpr int AGG_WORDS = 5;
+// rho (96 bits: 512 nodes of prefixes below 2^63), 40 bits per word under a tag
+// of 24, the low bits of the number of the launch that wrote it.  Every launch
+// writes every word, so that a word not yet written carries the tag before.
+// (32 bits beside a tag of 32 take a fifth word, and from 19456 nodes on a
+// larger workspace than callers have planned with.)
+constexpr int AGG_WORDS = 4;
 struct FieldAgg {
     unsigned long long w[AGG_WORDS];
 };
+constexpr int AGG_SHIFT = 40;
+constexpr unsigned long long AGG_MASK = (1ull << AGG_SHIFT) - 1;
+
+__host__ __device__ inline FieldAgg agg_pack(unsigned long long tag, long long A, unsigned long long B_lo,
+                                             long long B_hi)
+{
+    const unsigned long long a = (unsigned long long)A, t = tag << AGG_SHIFT;
+    return FieldAgg{{(a & AGG_MASK) | t, a >> 40 | (B_lo & 0xFFFFull) << 24 | t, (B_lo >> 16 & AGG_MASK) | t,
+                     B_lo >> 56 | ((unsigned long long)B_hi & 0xFFFFFFFFull) << 8 | t}};
+}
+
+__host__ __device__ inline void agg_unpack(const unsigned long long (&w)[AGG_WORDS], long long &A,
+                                           unsigned long long &B_lo, long long &B_hi)
+{
+    A = (long long)((w[0] & AGG_MASK) | w[1] << 40);
+    B_lo = (w[1] >> 24 & 0xFFFFull) | (w[2] & AGG_MASK) << 16 | w[3] << 56;
+    B_hi = (int32_t)(uint32_t)(w[3] >> 8);
+}
 
 // Read-only parameters and buffer pointers of one diode (device copy).
 struct Diode {

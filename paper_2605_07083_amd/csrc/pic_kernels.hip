@@ -1884,8 +1884,8 @@ __device__ __forceinline__ I128 wave_incl_scan_i128(I128 x)
 //   k_field_tiles  (larger grids) tiles of BIG_TILE nodes; a tile block
 //                  publishes its aggregates (A_t = sum of its charge, B_t =
 //                  sum over its interior nodes of the in-tile inclusive
-//                  prefix), every 32 bits of them beside the launch's epoch in
-//                  a 64-bit word, so that a reader needs no flag and neither
+//                  prefix), every 40 bits of them beside the launch's tag in a
+//                  64-bit word, so that a reader needs no flag and neither
 //                  side a cache write-back or invalidation, and combines the
 //                  aggregates of the tiles before it: P_t = sum_{u<t} A_u is
 //                  S1 before the tile, Q_t = sum_{u<t} (n_u P_u + B_u) is T
@@ -2627,6 +2627,7 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
     // averaged (the host sets avg_on between steps)
     const uint32_t step = mode == 0 ? (uint32_t)uni((int)fs.s_st.step) : 0u;
     const uint32_t epoch = fs.s_st.field_epoch;
+    const unsigned long long tag = (epoch + 1u) & ((1u << (64 - AGG_SHIFT)) - 1u);
     const int avg = uni(fs.s_st.avg_on);
     if (mode == 0) {
         field_step_plan(dd, parity, step, role, fs, keys);
@@ -2706,12 +2707,10 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
         }
         if (lane == TW - 1) {
             s_B = bi;
-            const uint32_t part[AGG_WORDS] = {(uint32_t)ai, (uint32_t)((unsigned long long)ai >> 32), (uint32_t)bi.lo,
-                                              (uint32_t)(bi.lo >> 32), (uint32_t)bi.hi};
+            const FieldAgg own = agg_pack(tag, ai, bi.lo, bi.hi);
 #pragma unroll
             for (int k = 0; k < AGG_WORDS; ++k)
-                __hip_atomic_store(glb(&agg[t].w[k]), (unsigned long long)(epoch + 1u) << 32 | part[k], __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(glb(&agg[t].w[k]), own.w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // the tiles before this one, one lane each: P_u = sum_{v<u} A_v, the
         // sum of S1 over tile u's interior nodes n_u P_u + B_u, and their sums
@@ -2726,14 +2725,12 @@ __global__ __launch_bounds__(FT) void k_field_tiles(const Diode *__restrict__ D,
 #pragma unroll
                 for (int k = 0; k < AGG_WORDS; ++k) {
                     g[k] = __hip_atomic_load(glb(&agg[u].w[k]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    all = all && (uint32_t)(g[k] >> 32) == epoch + 1u;
+                    all = all && g[k] >> AGG_SHIFT == tag;
                 }
                 if (all) break;
                 __builtin_amdgcn_s_sleep(1);
             }
-            Au = (long long)((g[0] & 0xFFFFFFFFull) | g[1] << 32);
-            Bu.lo = (g[2] & 0xFFFFFFFFull) | g[3] << 32;
-            Bu.hi = (long long)(int32_t)(uint32_t)g[4];
+            agg_unpack(g, Au, Bu.lo, Bu.hi);
             nu = max(0, min((u + 1) * BIG_TILE, N) - max(u * BIG_TILE, 1));
         }
         const long long Pu = wave_incl_scan_i64(Au) - Au;

@@ -148,3 +148,14 @@ def test_surrogate_workspace_fits_what_callers_planned(batch, cells, planned):
     """A workspace that was once large enough for a handle still is."""
     from paper_2605_07083_amd import surrogate
     assert surrogate.workspace_size(batch, cells) <= planned
+
+
+@pytest.mark.parametrize("diodes,cells,load,planned",
+                         [(1, 2, 1, 1652480), (1, 256, 25600, 9618176), (3, 2048, 409600, 405446912),
+                          (1, 2049, 1000, 1873664), (2, 4096, 100000, 69365504), (1, 16384, 16384000, 5350742784),
+                          (1, 19455, 1000, 3750912), (1, 19456, 1000, 3754752), (5, 24000, 5000, 27493632),
+                          (1, 32767, 32767, 15634176), (48, 32767, 1000, 249065984)])
+def test_workspace_fits_what_callers_planned(diodes, cells, load, planned):
+    """A workspace that was once large enough for these diodes still is."""
+    cfgs = [presets.scaled(presets.tiny(), N=cells, n_load=load, diode=d) for d in range(diodes)]
+    assert pic.pic_workspace_size(cfgs) <= planned

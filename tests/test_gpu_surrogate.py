@@ -484,3 +484,26 @@ def test_training_within_its_workspace(sur, torch, B, X):
         net.close()
     assert got[0][0] == got[1][0]
     assert all(np.array_equal(x, y) for x, y in zip(got[0][1], got[1][1]))
+
+
+@pytest.mark.parametrize("cells,electrons,ions", [(2049, 1.0, 0.0), (2560, 0.0, 1.0), (4607, 0.9, 1.0),
+                                                  (19456, 1.0, 0.1), (32767, 0.0, 1.0), (32767, 1.0, 0.0)])
+def test_field_of_tiled_grids(torch, O, cells, electrons, ions):
+    """The tiles' aggregates on grids from five tiles to sixty-four, of bare
+    charge of either sign (every word of a negative sum has its high bits set)
+    and of near balance, over a few launches, against the exact rational solve
+    (an FP64 sweep is off by more than the tolerance on the largest grids)."""
+    from paper_2605_07083_amd import pic
+    cfg = presets.scaled(presets.tiny(), N=cells, n_load=cells * 30, gamma_emit=1e21)
+    ne, ni = _profiles(cfg, 5)
+    dens = np.stack([ne * electrons, ni * ions])[None]
+    _say("case: field of %d cells, electrons %.1f, ions %.1f" % (cells, electrons, ions))
+    h = pic.Handle(cfg, densities=torch.tensor(dens, dtype=torch.float64, device="cuda:0"))
+    for steps in (0, 1, 3):
+        h.step(steps)
+        st, t = gpu_state(h, 0)
+        assert deposit_matches(O, cfg, h, st, 0) == []
+        h.refield()
+        assert field_matches(O, cfg, h, oracle_from_gpu(O, cfg, st, t), 0, exact=True) == []
+    assert restart_step_check(O, cfg, h, 2, exact_field=True) == []
+    h.close()
