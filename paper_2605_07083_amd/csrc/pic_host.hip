@@ -437,27 +437,39 @@ namespace {
 
 // The schedule when the caller names none.  A CU holds four of the particle
 // kernel's blocks (three with four particles per thread), so 1024 (768) blocks
-// are one round.  Particles per thread: as few as let every block have one
-// chunk in one round; two where none does.  Measured, us per step with one /
-// two / four (2048 cells, best grid): 0.20M particles 18.0 / 18.4 / 20.2, 0.39M
-// 20.6 / 19.7 / 21.3, 0.69M 22.7 / 22.9 / 22.4, 0.79M 23.5 / 23.7 / 22.7,
-// 0.99M 24.6 / 23.0 / 25.8.
+// are one round.  Particles per thread: as few as let every chunk of the loads
+// have a block of one round, two where none does.  Measured, us per step on 1024
+// blocks with one / two / four (one diode of 2048 cells): 0.20M particles loaded
+// 15.1 / 15.7 / 17.2, 0.26M 15.6 / 15.9 / 17.9, 0.30M 17.6 / 16.8 / 17.6, 0.50M
+// 18.2 / 17.2 / 18.2, 0.62M 20.0 / 19.7 / 19.3.  The last line, two / four, by
+// chunks of 1024 live particles: 8192 cells 753 18.1 / 18.6, 763 18.0 / 18.4, 773
+// 18.2 / 20.6, 793 18.6 / 21.4; 512 cells 753 19.8 / 18.2, 762 19.3 / 18.1, 772
+// 20.5 / 20.6, 781 19.2 / 21.0; the paper's diode 765 19.5 / 19.3, 774 19.4 /
+// 20.2.  Diodes that lose electrons to the walls at once get there with up to 6 %
+// more loaded (2048 cells, 810 loaded, 762 live: 20.1 / 19.7); those that keep
+// them would pay 14 % for that.  The newborns' tails are not counted: with 16
+// diodes they move the line down by a few chunks (734 live 20.3 / 19.6, 744
+// 19.8 / 21.7), with four or fewer not at all.
 int ppt_for(const pic_handle *h)
 {
-    int64_t total = 0;
-    for (int d = 0; d < h->nd; ++d) total += 2 * h->cfg[d].n_load;
-    if (total <= 1024 * 256) return 1;
-    return total > 1024 * 512 && total <= 800 * 1024 ? 4 : 2;
+    for (int ppt : {1, 2, 4}) {
+        int64_t chunks = 0;
+        for (int d = 0; d < h->nd; ++d) chunks += 2 * ((h->cfg[d].n_load + 256 * ppt - 1) / (256 * ppt));
+        if (chunks <= (ppt == 4 ? 768 : 1024)) return ppt;
+    }
+    return 2;
 }
 
 // Grid: one round of blocks is best while a block's share stays short (a
 // block's run works off its rare items at its end, and with every block in one
-// round nothing else runs meanwhile).  Above 20 chunks a block, eight chunks a
-// block in several rounds.  Measured, us per step at 1024 / 1536 / 2048 / 4096
-// / 8192 blocks: 2048 cells, 1.5k chunks 24.1 / 26.2 / 26.2 / 26.5 / 31; the
-// paper's diode, 16k chunks 57 / 65 / 59 / 64 / 84; eleven diodes, 30k chunks
-// 118 / 123 / 115 / 103 / 113; the sweep, 42k chunks 159 / 158 / 154 / 148 /
-// 150 (141 at 6144); the large diode, 63k chunks 219 / 213 / 212 / 185 / 184.
+// round nothing else runs meanwhile).  1024 with four particles per thread too:
+// the blocks beyond one round find no chunk there and end (768 took the same).
+// Above 20 chunks a block, eight chunks a block in several rounds.  Measured, us
+// per step at 1024 / 1536 / 2048 / 4096 / 8192 blocks: 2048 cells, 1.5k chunks
+// 24.1 / 26.2 / 26.2 / 26.5 / 31; the paper's diode, 16k chunks 57 / 65 / 59 /
+// 64 / 84; eleven diodes, 30k chunks 118 / 123 / 115 / 103 / 113; the sweep, 42k
+// chunks 159 / 158 / 154 / 148 / 150 (141 at 6144); the large diode, 63k chunks
+// 219 / 213 / 212 / 185 / 184.
 int grid_for(const pic_handle *h)
 {
     int64_t chunks = 0;

@@ -504,3 +504,31 @@ def test_read_memory_passes_from_handle_to_handle(pic):
         for k, (t, f) in ex.map(one, range(48)):
             assert all(np.array_equal(f[q], want[k][1][q]) for q in f)
             assert all(np.array_equal(t[q], want[k][0][q]) for q in t if q != "abs_energy")
+
+
+def _default_ppt(loads):
+    """As few particles per thread as let every chunk of 256 threads have a
+    block of one round (four blocks per CU, three with four particles per
+    thread), counted by the loads; else two."""
+    for ppt, blocks in ((1, 4 * 256), (2, 4 * 256), (4, 3 * 256)):
+        if sum(2 * -(-n // (256 * ppt)) for n in loads) <= blocks:
+            return ppt
+    return 2
+
+
+@pytest.mark.parametrize("loads", [[25600], [131072], [131073], [262144], [262145], [393216], [393217], [409600],
+                                   [420000], [2048000], [12288] * 16, [24320] * 16, [24577] * 16, [100] * 256, [1] * 3])
+def test_default_particles_per_thread_by_rounds_of_blocks(pic, loads):
+    """Loads on either side of each line of the default schedule, and a few
+    steps on it equal to those on another schedule."""
+    cfgs = [presets.scaled(presets.tiny(), n_load=n, diode=d) for d, n in enumerate(loads)]
+    a, b = pic.Handle(cfgs), pic.Handle(cfgs)
+    t = a.tuning()
+    assert t["ppt"] == _default_ppt(loads) and t["grid"] == 1024
+    b.set_tuning(ppt=4 if t["ppt"] != 4 else 2, grid=2048)
+    for h in (a, b):
+        h.step(5)
+    for d in {0, len(loads) - 1}:
+        assert all(np.array_equal(a.hist(d, s), b.hist(d, s)) for s in range(3))
+    a.close()
+    b.close()
