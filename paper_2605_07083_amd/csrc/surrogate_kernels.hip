@@ -23,12 +23,12 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "net_tanh.h"
+
 namespace sur {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int KS = 5;     // kernel size
 constexpr int OUT = 39;   // output channels: phi / V, ln n_e / n0, ln n_i / n0, 36 velocity quantiles
@@ -629,44 +629,6 @@ struct NetParams {
     const __bf16 *w[6];      // forward weights, fragment order
     const float *bias[6];
 };
-
-// bf16(tanhf(x)) of four values.  tanh x = 1 - 2 / (1 + e^2x) from the
-// hardware's exp2 and reciprocal is off by a few 1e-7 in absolute terms; the
-// two ends of that error interval almost always round to the same bfloat16,
-// which then is the one tanhf's result rounds to (checked for every float x;
-// half the absolute part of this margin still held).  Where they differ, for
-// one value in some thousands, tanhf itself decides.  About 13 instructions'
-// time per value instead of tanhf's 35.
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
-{
-    const bf16x2 r = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(uint32_t, r);
-}
-
-// The value, and what is open: nonzero bits of `open` where the ends differ.
-__device__ __forceinline__ uint2 tanh4(f32x4 x, uint2 &open)
-{
-    constexpr float MARGIN = 1.2e-7f;
-    float lo[4], hi[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float t = __builtin_amdgcn_exp2f(x[i] * 2.8853900817779268f);   // 2 / ln 2
-        const float r = __builtin_amdgcn_rcpf(t + 1.0f);
-        lo[i] = __builtin_fmaf(-2.0f * (1.0f + MARGIN), r, 1.0f - MARGIN);
-        hi[i] = __builtin_fmaf(-2.0f * (1.0f - MARGIN), r, 1.0f + MARGIN);
-    }
-    const uint2 a = make_uint2(pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]));
-    open = make_uint2(a.x ^ pack_bf16(hi[0], hi[1]), a.y ^ pack_bf16(hi[2], hi[3]));
-    return a;
-}
-
-// tanhf where it is open in some lane (a lane whose ends agree gets the same
-// bits from it).
-__device__ __forceinline__ void tanh4_settle(f32x4 x, uint2 open, uint2 &h)
-{
-    if (__any(open.x)) h.x = pack_bf16(tanhf(x[0]), tanhf(x[1]));
-    if (__any(open.y)) h.y = pack_bf16(tanhf(x[2]), tanhf(x[3]));
-}
 
 // the caller's arrays need no more than their elements' alignment
 typedef float out_f32x4 __attribute__((__vector_size__(16), aligned(4)));
