@@ -173,79 +173,7 @@ __device__ __forceinline__ unsigned long long fixed_right(double f)
     return r >= TWO32 ? (1ull << 32) : (unsigned long long)(unsigned int)r;
 }
 
-__device__ __forceinline__ int wave_min(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ int wave_max(int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-// Block-wide min and max (every thread receives both).
-__device__ __forceinline__ void block_minmax(int &mn, int &mx, int *sh)
-{
-    mn = wave_min(mn);
-    mx = wave_max(mx);
-    int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) { sh[w] = mn; sh[NW + w] = mx; }
-    __syncthreads();
-    mn = sh[0]; mx = sh[NW];
-#pragma unroll
-    for (int q = 1; q < NW; ++q) { mn = min(mn, sh[q]); mx = max(mx, sh[NW + q]); }
-    __syncthreads();
-}
-
-
-// ---------------------------------------------------------------------------
-// Wave-level run reductions.  Cell-sorted particles put long runs of equal
-// cells in consecutive lanes; combining each run before touching LDS turns a
-// 64-way same-address atomic into one atomic per run.
-// ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
-
-// Segmented inclusive sums of (L, A) over runs of equal key in consecutive
-// lanes; 'last' marks the final lane of each run, which then holds the run sums.
-__device__ __forceinline__ void run_sums(int key, unsigned long long &L, unsigned long long &A, bool &last)
-{
-    const int lane = lane_id();
-    const int prev = __shfl_up(key, 1, 64);
-    const int next = __shfl_down(key, 1, 64);
-    int flag = (lane == 0 || prev != key) ? 1 : 0;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned long long Lo = __shfl_up(L, o, 64), Ao = __shfl_up(A, o, 64);
-        const int fo = __shfl_up(flag, o, 64);
-        if (lane >= o) {
-            if (!flag) { L += Lo; A += Ao; }
-            flag |= fo;
-        }
-    }
-    last = (lane == 63) || (next != key);
-}
-
-// Start lane and length of the run of equal keys that contains this lane.
-__device__ __forceinline__ void run_extent(int key, int &start, int &len)
-{
-    const int lane = lane_id();
-    const int prev = __shfl_up(key, 1, 64);
-    const int next = __shfl_down(key, 1, 64);
-    int s = (lane == 0 || prev != key) ? lane : 0;
-    int e = (lane == 63 || next != key) ? lane : 63;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(s, o, 64);
-        const int u = __shfl_down(e, o, 64);
-        if (lane >= o) s = max(s, t);
-        if (lane + o < 64) e = min(e, u);
-    }
-    start = s;
-    len = e - s + 1;
-}
 
 // ---------------------------------------------------------------------------
 // Chunk maps of the particle kernel (tails first, below) and the re-sort.
@@ -680,27 +608,9 @@ __device__ __forceinline__ void fold_tally_copies(const RareTally &v, RareTally 
     if (last) rt->ion_lost = t;
 }
 
-// Add a step's tally to the diode's cumulative tallies (one thread; atomics
-// without return, so nothing waits for the old values).
-__device__ __forceinline__ void apply_tally(const Diode &dd, const RareTally &t)
-{
-    DiodeTally *T = dd.tally;
-    for (int ion = 0; ion < 2; ++ion)
-        if (t.cand[ion]) atomicAdd(&T->cand[ion], (unsigned long long)t.cand[ion]);
-#pragma unroll
-    for (int k = 0; k < NCH; ++k)
-        if (t.coll[k]) atomicAdd(&T->coll[k], (unsigned long long)t.coll[k]);
-#pragma unroll
-    for (int sp = 0; sp < NSP; ++sp)
-        for (int w = 0; w < 2; ++w)
-            if (t.abs_count[sp][w]) {
-                atomicAdd(&T->abs_count[sp][w], (unsigned long long)t.abs_count[sp][w]);
-                atomicAdd(&T->abs_energy[sp][w], t.abs_energy[sp][w]);
-            }
-}
-
-// apply_tally by the first wave, a lane per field.
-__device__ __forceinline__ void apply_tally_wave(const Diode &dd, const RareTally &t, int lane)
+// Add a step's tally to the diode's cumulative tallies: by the first wave, a
+// lane per field (atomics without return, so nothing waits for the old values).
+__device__ __forceinline__ void apply_tally(const Diode &dd, const RareTally &t, int lane)
 {
     static_assert(offsetof(RareTally, coll) == 8 && offsetof(RareTally, abs_count) == 8 + 4 * NCH, "lanes by field");
     DiodeTally *T = dd.tally;
@@ -1851,10 +1761,9 @@ __device__ __forceinline__ I128 wave_incl_scan_i128(I128 x)
 // phi_j = V j / N + alpha (j T_N - N T_j) / N: the direct solution of the
 // constant-coefficient Dirichlet system, rounded once at the end.
 // ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // Sources and field of a step in one kernel per step.
 //
-// Grid (tiles + 1, diodes).  Block 0 of a diode writes the newborn records
+// Grid (tiles + 2, diodes).  Block 0 of a diode writes the newborn records
 // (and works off any rare items the particle kernel spilled to the global
 // lists, normally none; the other blocks wait for its flag before they read
 // the counters those items change).  Block t + 1 takes tile t of the nodes:
@@ -1894,7 +1803,8 @@ __device__ __forceinline__ I128 wave_incl_scan_i128(I128 x)
 //                  last tile (the writer) has T_N and stores the correction
 //                  phi_j = phi'_j + j c, c = alpha T_N / N, which shifts every
 //                  node's E by -c / dz.  The particle kernel adds that shift
-//                  to the E it gathers, the host adds both to what it reads.
+//                  to the E it gathers, k_read_fields j c to the potential it
+//                  reads back, pic_get_efield the shift to the field.
 // ---------------------------------------------------------------------------
 constexpr int TILE = 512;                 // nodes per tile block of k_field_step
 // Every node's charge staged in each block's LDS.  Above 2049 nodes the tiles'
@@ -2169,8 +2079,8 @@ __device__ __forceinline__ void field_step_plan(const Diode &dd, int parity, uin
             // flag (a barrier does not wait for other waves' global stores)
             __threadfence();
             __syncthreads();
+            if (tid < 64) apply_tally(dd, fs.rs, tid);
             if (tid == 0) {
-                apply_tally(dd, fs.rs);
                 if (fs.rs.ion_lost) atomicAdd(&st->ion_lost, fs.rs.ion_lost);
                 __hip_atomic_store(glb(&st->spill_flag), step + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -2245,7 +2155,7 @@ __device__ __forceinline__ void field_step_tail(const Diode &dd, FieldShared &fs
     __syncthreads();
     if (tid < 64) {
         dd.tacc[tid].t = RareTally{};
-        apply_tally_wave(dd, fs.rt, tid);
+        apply_tally(dd, fs.rt, tid);
     }
     if (tid == 0) {
         const BirthPlan &p = fs.bp;
