@@ -205,7 +205,9 @@ int pic_init_from_profiles(const pic_config *cfgs, int n_diodes, void *dev_works
 int pic_init_from_state(const pic_config *cfgs, int n_diodes, void *dev_workspace, size_t bytes,
                         void *hip_stream, const double *dev_state, pic_handle **out);
 
-/* Advance every diode nsteps steps.  Asynchronous on the bound stream. */
+/* Advance every diode nsteps steps.  Asynchronous on the bound stream.  Whole
+ * re-sort periods are replayed from a HIP graph, other steps launched one by
+ * one (see pic_set_tuning). */
 int pic_step(pic_handle *h, int64_t nsteps);
 
 /* Synchronise the bound stream; return the first sticky device error, if any. */
@@ -290,14 +292,14 @@ int pic_refield(pic_handle *h);
 
 /* Per-kernel timing: run nsteps steps on the current schedule -- with graph
  * replay, each run up to the next re-sort boundary is one replayed graph
- * (pic_step replays whole re-sort periods only) -- with HIP events around launches of the particle kernel on
- * the bound stream (with graph replay: the particle kernels of up to 8 steps
- * spread evenly over each replayed run, at most 4096 in all; on the plain
- * stream, where each pair of timestamps stalls the launches around it, at
- * most 32: every launch when nsteps <= w, else one in s = ceil(nsteps / w)
- * rounded up to an odd number, w = min(32, max(4, nsteps / 16))) and return
- * their mean duration and the time from the first enqueued step to the end
- * of the last (ms).
+ * (pic_step replays whole re-sort periods only) -- with HIP events around
+ * launches of the particle kernel on the bound stream (with graph replay: the
+ * particle kernels of up to 8 steps spread evenly over each replayed run, at
+ * most 4096 in all; on the plain stream, where each pair of timestamps stalls
+ * the launches around it, at most 32: every launch when nsteps <= w, else one
+ * in s = ceil(nsteps / w) rounded up to an odd number, w = min(32, max(4,
+ * nsteps / 16))) and return their mean duration and the time from the first
+ * enqueued step to the end of the last (ms).
  * Events are created on first use and kept by the handle.  Synchronises at
  * the end only. */
 int pic_step_timed(pic_handle *h, int64_t nsteps, double *particle_kernel_ms, double *total_ms);
@@ -305,8 +307,11 @@ int pic_step_timed(pic_handle *h, int64_t nsteps, double *particle_kernel_ms, do
 /* Launch schedule of the hot loop: particles per thread in the particle and
  * sort kernels (1, 2, 4 or 8; 0 keeps), persistent grid size (0: default),
  * re-sort period in steps (0 keeps) and whether full re-sort periods are
- * replayed from a captured HIP graph (-1 keeps).  Results do not depend on
- * these choices.  Synchronises. */
+ * replayed from a captured HIP graph (-1 keeps).  A period is replayed when one
+ * pic_step covers all of it: calls of fewer steps than the period, and the
+ * steps before its first and after its last boundary in any call, are launched
+ * one by one whatever use_graph says (6 us of the host's time a step).
+ * Results do not depend on these choices.  Synchronises. */
 int pic_set_tuning(pic_handle *h, int ppt, int grid, int sort_period, int use_graph);
 int pic_get_tuning(pic_handle *h, int *ppt, int *grid, int *sort_period, int *use_graph);
 

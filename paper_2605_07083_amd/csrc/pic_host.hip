@@ -634,7 +634,8 @@ int get_graph(pic_handle *h, int p, bool sorted, int64_t r, bool timed, GraphEnt
 // Enqueue nsteps steps.  With graph replay every whole re-sort period is one
 // graph launch; the steps before the first boundary and after the last one
 // are launched on the stream.  (Launched, a step costs the host 6 us, less
-// than the smallest diode's 15.5 us on the GPU, and runs as fast as replayed.
+// than the smallest diode's 13.1 us on the GPU, and runs as fast as replayed:
+// periods of 16 to 1000 steps in blocks of 1 to 1000, within 2 % either way.
 // Capturing such runs too, one graph per length, left a program that steps
 // 100 at a time with more lengths than the cache holds, captured anew nearly
 // every call: 18.3 against 16.2 us per step on the smallest diode; and a call

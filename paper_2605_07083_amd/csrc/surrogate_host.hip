@@ -243,7 +243,8 @@ int copy_out(sur_net *n, bool grads, float *w, float *b)
     return PIC_OK;
 }
 
-// The most cells per sample that sur_forward_noalloc takes.
+// The most cells per sample that sur_forward_noalloc takes: a limit of its
+// interface.  Nothing in the forward pass needs it (the activations are in LDS).
 constexpr int NOALLOC_MAX_CELLS = 17096;
 
 }  // namespace
@@ -336,8 +337,8 @@ int sur_forward_noalloc(sur_net *n, const float *dev_params, int batch, float *d
     if (!n || !dev_params || !dev_out) return fail(PIC_EINVAL, "bad arguments");
     if (batch < 1) return fail(PIC_EINVAL, "batch must be positive");
     if (n->X > NOALLOC_MAX_CELLS)
-        return fail(PIC_EINVAL, "cells beyond the allocation-free path's scratch limit: at most " +
-                                    std::to_string(NOALLOC_MAX_CELLS) + " per sample");
+        return fail(PIC_EINVAL, "sur_forward_noalloc takes at most " + std::to_string(NOALLOC_MAX_CELLS) +
+                                    " cells per sample (sur_forward, which needs no scratch either, takes more)");
     int dev = -1;
     SUR_TRY(hipGetDevice(&dev));
     if (dev != n->device) return fail(PIC_EINVAL, "the handle's GPU is not the current device");

@@ -622,8 +622,8 @@ __global__ void k_init_weights(float *__restrict__ wm, int cin, int coutp, int c
 // matrix cores 1/3), on one sample by the chain of layers.  One kernel per
 // layer was bound by its launches and by every activation written and read
 // again in FP32 and bfloat16.  Measured (2048 cells, the whole call, before and
-// after): 1 sample 53 -> 7.9 us, 8 samples 58 -> 14.3, 64 samples 131 -> 43 us
-// (610 TFLOP/s).
+// after): 1 sample 53 -> 7.7 us, 8 samples 58 -> 14.3, 64 samples 135 -> 40.3 us
+// (650 TFLOP/s).
 // ---------------------------------------------------------------------------
 struct NetParams {
     const __bf16 *w[6];      // forward weights, fragment order
