@@ -464,17 +464,21 @@ int ppt_for(const pic_handle *h)
 // block's run works off its rare items at its end, and with every block in one
 // round nothing else runs meanwhile).  1024 with four particles per thread too:
 // the blocks beyond one round find no chunk there and end (768 took the same).
-// Above 20 chunks a block, eight chunks a block in several rounds.  Measured, us
-// per step at 1024 / 1536 / 2048 / 4096 / 8192 blocks: 2048 cells, 1.5k chunks
-// 24.1 / 26.2 / 26.2 / 26.5 / 31; the paper's diode, 16k chunks 57 / 65 / 59 /
-// 64 / 84; eleven diodes, 30k chunks 118 / 123 / 115 / 103 / 113; the sweep, 42k
-// chunks 159 / 158 / 154 / 148 / 150 (141 at 6144); the large diode, 63k chunks
-// 219 / 213 / 212 / 185 / 184.
+// Above 16 chunks a block, eight chunks a block in several rounds.  Measured, us
+// per step at 1024 / 2048 / 3072 / 4096 blocks: the paper's diode, 8k chunks 34 /
+// 39 / 40 / 46, 16k 54 / 57 / 58 / 62, 20k 67 / 68 / 70 / 70; 8192 cells, 16k 57 /
+// 59 / 60 / 64; four diodes of 2048 cells with every collision channel, 8k 46 /
+// 41 / 42 / 46, 16k 75 / 64 / 62 / 63, 20k 87 / 76 / 72 / 72.  At 16k one round
+// costs such batches no more than 8192 blocks would (87), at 18k up to 8 % more
+// (86 against 80), and what it gives the others has fallen to 3 %.  Far above, at
+// 1024 / 2048 / 4096 / 8192 blocks: eleven diodes, 30k chunks 118 / 115 / 103 /
+// 113; the sweep, 42k 159 / 154 / 148 / 150 (141 at 6144); the large diode, 63k
+// 219 / 212 / 185 / 184.
 int grid_for(const pic_handle *h)
 {
     int64_t chunks = 0;
     for (int d = 0; d < h->nd; ++d) chunks += 2 * ((h->cfg[d].n_load + 256 * h->ppt - 1) / (256 * h->ppt));
-    if (chunks <= 20 * 1024) return 1024;
+    if (chunks <= 16 * 1024) return 1024;
     return (int)std::min<int64_t>(8192, (chunks / 8 + 1023) / 1024 * 1024);
 }
 

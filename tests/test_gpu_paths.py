@@ -532,3 +532,20 @@ def test_default_particles_per_thread_by_rounds_of_blocks(pic, loads):
         assert all(np.array_equal(a.hist(d, s), b.hist(d, s)) for s in range(3))
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("loads,grid", [([4194304], 1024), ([4194305], 2048), ([1048576] * 4, 1024),
+                                        ([1200000] * 4, 3072), ([500] * 256, 1024), ([16384000], 8192)])
+def test_default_grid_by_chunks(pic, loads, grid):
+    """One round of blocks up to sixteen chunks a block, eight chunks a block
+    above (8192 blocks at most), at the default particles per thread; the loaded
+    diodes' charge is all deposited."""
+    cfgs = [presets.scaled(presets.tiny(), n_load=n, diode=d) for d, n in enumerate(loads)]
+    h = pic.Handle(cfgs)
+    assert h.tuning()["grid"] == grid
+    h.step(1)
+    h.refield()
+    for d in {0, len(loads) - 1}:
+        n = h.tally(d)["n_live"]
+        assert all(int(h.hist(d, s).sum()) == int(n[s]) << 32 for s in range(3))
+    h.close()
