@@ -128,7 +128,7 @@ void layout(sur_net &n, Bump &bp)
         L.wb = bp.take<__bf16>((size_t)L.cin * L.kpb);
     }
     n.loss = bp.take<double>(1);
-    n.param_bytes = bp.off;
+    n.param_bytes = align_up(bp.off);    // cleared whole: a tail of 8 bytes would be a launch of its own
     n.feat = bp.take<__bf16>(P * SUR_IN);
     for (int k = 0; k < 2; ++k) n.dz[k] = bp.take<__bf16>(P * SUR_HIDDEN);
     // One region for the forward blocks' shares of the loss, the partial
