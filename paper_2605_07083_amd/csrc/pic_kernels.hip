@@ -1238,15 +1238,20 @@ __global__ __launch_bounds__(256) void k_profile_clear(const Diode *__restrict__
 // block: the counts' clearing and flush is what a block costs (1024 blocks of
 // 256 threads took 13.5 us over 2547 particles and 17.0 us over 4.1 million;
 // this takes 4.6 us and 9.6 us, eight particles ahead 10.1 us, 256 threads
-// with eight 13.5 us).
-constexpr int PH_THREADS = 1024, PH_AHEAD = 4, PH_BLOCKS = 256;
+// with eight 13.5 us).  With few bins the adds to one address queue up, the more
+// the larger the block: a bin then has several counts, by the thread's lane, as
+// many as PH_WORDS hold (5 bins, with one count each and so: 25600 particles 6.2
+// and 3.6 us, blocks of 256 threads 5.0; 4.1 million 19.1 and 10.6 us).
+constexpr int PH_THREADS = 1024, PH_AHEAD = 4, PH_BLOCKS = 256, PH_WORDS = 2048, PH_MAX_SHIFT = 5;
+static_assert(PH_WORDS <= 2 * PH_THREADS, "a thread per bin where a bin has several counts");
 __global__ __launch_bounds__(PH_THREADS) void k_phase_hist(const Diode *__restrict__ D,
                                                            const DiodeState *__restrict__ S, int d, int s, int parity,
                                                            int nz, int nv, double sz, double vmin, double sv,
-                                                           unsigned long long *__restrict__ out)
+                                                           int shift, unsigned long long *__restrict__ out)
 {
-    extern __shared__ uint32_t ph_hist[];
+    extern __shared__ uint32_t ph_hist[];      // 2^shift counts per bin
     const int W = nv + 2, nb = nz * W, tid = threadIdx.x;
+    const int copies = 1 << shift, copy = tid & (copies - 1);
     const SpeciesBuf b0 = D[d].buf[0][s], b1 = D[d].buf[1][s];
     const int n = S[d].n[s];
     const bool second = (parity ^ S[d].flip[s]) != 0;
@@ -1265,7 +1270,7 @@ __global__ __launch_bounds__(PH_THREADS) void k_phase_hist(const Diode *__restri
         }
     };
     fetch(i0);
-    for (int i = tid; i < nb; i += PH_THREADS) ph_hist[i] = 0u;
+    for (int i = tid; i < nb << shift; i += PH_THREADS) ph_hist[i] = 0u;
     __syncthreads();
     for (int base = i0; base < i1; base += PH_AHEAD * PH_THREADS) {
         int bin[PH_AHEAD];
@@ -1280,12 +1285,18 @@ __global__ __launch_bounds__(PH_THREADS) void k_phase_hist(const Diode *__restri
         if (base + PH_AHEAD * PH_THREADS < i1) fetch(base + PH_AHEAD * PH_THREADS);
 #pragma unroll
         for (int k = 0; k < PH_AHEAD; ++k)
-            if (bin[k] >= 0) atomicAdd(&ph_hist[bin[k]], 1u);
+            if (bin[k] >= 0) atomicAdd(&ph_hist[(bin[k] << shift) + copy], 1u);
     }
     __syncthreads();
-    for (int i = tid; i < nb; i += PH_THREADS) {
-        const uint32_t c = ph_hist[i];
+    auto add = [&](int i, uint32_t c) {
         if (c) atomicAdd(&out[i], (unsigned long long)c);
+    };
+    if (shift == 0) {
+        for (int i = tid; i < nb; i += PH_THREADS) add(i, ph_hist[i]);
+    } else if (tid < nb) {
+        uint32_t c = 0u;
+        for (int k = 0; k < copies; ++k) c += ph_hist[(tid << shift) + ((k + tid) & (copies - 1))];   // banks apart
+        add(tid, c);
     }
 }
 
@@ -1293,11 +1304,14 @@ extern "C" hipError_t picx_launch_phase_hist(const Diode *D, const DiodeState *S
                                              int nv, double sz, double vmin, double sv, unsigned long long *out,
                                              int64_t capacity, hipStream_t st)
 {
-    const size_t lds = (size_t)nz * (nv + 2) * sizeof(uint32_t);
+    const int nb = nz * (nv + 2);
+    int shift = 0;
+    while (shift < PH_MAX_SHIFT && nb << (shift + 1) <= PH_WORDS) ++shift;
+    const size_t lds = ((size_t)nb << shift) * sizeof(uint32_t);
     const int64_t rounds = (capacity + PH_THREADS * PH_AHEAD - 1) / (PH_THREADS * PH_AHEAD);
     const int blocks = (int)std::min<int64_t>(PH_BLOCKS, std::max<int64_t>(1, rounds));
     hipLaunchKernelGGL(k_phase_hist, dim3(blocks), dim3(PH_THREADS), lds, st, D, S, d, s, parity, nz, nv, sz, vmin, sv,
-                       out);
+                       shift, out);
     return hipGetLastError();
 }
 

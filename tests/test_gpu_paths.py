@@ -549,3 +549,21 @@ def test_default_grid_by_chunks(pic, loads, grid):
         n = h.tally(d)["n_live"]
         assert all(int(h.hist(d, s).sum()) == int(n[s]) << 32 for s in range(3))
     h.close()
+
+
+@pytest.mark.parametrize("nz,nv", [(1, 1), (1, 3), (2, 30), (1, 63), (8, 30), (16, 62), (5, 203), (32, 62), (1, 2047)])
+def test_phase_space_of_few_bins(pic, O, nz, nv):
+    """Bins counted in 32 places each, in fewer, and in one (from 1025 bins on),
+    over loads of a few particles, of one block and of several."""
+    cfg = presets.scaled(presets.tiny(), n_load=7)
+    for n_load in (7, 4097, 40961):
+        h = pic.Handle(dict(cfg, n_load=n_load))
+        h.step(3)
+        for sp, v in ((0, 2e6), (2, 2e4)):
+            out = h.phase_space(0, sp, nz, nv, -v, v)
+            h.phase_space(0, sp, nz, nv, -v, v, out)
+            h.sync()
+            p = h.particles(0, sp)
+            want = O.phase_space(p["z"], p["vz"], cfg["L"], nz, nv, -v, v)
+            assert np.array_equal(out.cpu().numpy(), 2 * want)
+        h.close()
