@@ -39,7 +39,7 @@ extern "C" hipError_t picx_launch_read_fields(const Diode *D, int d, int nodes, 
                                               hipStream_t st);
 extern "C" int picx_sources_field_kernels(int max_nodes, int mode);
 extern "C" hipError_t picx_launch_profile_load(const Diode *D, const double *dens, int rows, int nd, int max_cells,
-                                               hipStream_t s);
+                                               int64_t per_cell, hipStream_t s);
 extern "C" hipError_t picx_launch_sort(const Diode *D, DiodeState *S, int nd, int ppt, int grid, int parity,
                                        hipStream_t s);
 
@@ -886,8 +886,12 @@ static int init_impl(const pic_config *cfgs, int n_diodes, void *dev_workspace, 
             return cleanup(fail(PIC_EHIP, "load launch failed"));
     } else {
         int max_cells = 0;
-        for (int d = 0; d < n_diodes; ++d) max_cells = std::max(max_cells, cfgs[d].N);
-        if (picx_launch_profile_load(h->dD, dens, rows, n_diodes, max_cells, h->stream) != hipSuccess)
+        int64_t per_cell = 0;
+        for (int d = 0; d < n_diodes; ++d) {
+            max_cells = std::max(max_cells, cfgs[d].N);
+            per_cell = std::max<int64_t>(per_cell, cfgs[d].n_load / cfgs[d].N);
+        }
+        if (picx_launch_profile_load(h->dD, dens, rows, n_diodes, max_cells, per_cell, h->stream) != hipSuccess)
             return cleanup(fail(PIC_EHIP, "profile load launch failed"));
     }
     // the staging vectors die here: wait for the copies

@@ -1106,16 +1106,20 @@ __device__ __forceinline__ double from_q9(const double *q, const QuantileTable &
 // gathered from LDS.  A wave per cell sorted them in every lane, picked them
 // by selects and left a quarter of the lanes idle at 200 particles per cell:
 // 6.5 million particles (eight diodes) 158 us, now 106 us.
-constexpr int PF_CELLS = 8, PF_ROWS = 18;
+// Where the cells are too few to fill the chip, `split` blocks share their
+// particles (16 cells of 100000 per species, the whole creation of the diode:
+// 3.5 ms with one, 0.16).
+constexpr int PF_CELLS = 8, PF_ROWS = 18, PF_BLOCKS = 1024;
 __global__ __launch_bounds__(256) void k_profile_fill(const Diode *__restrict__ D, const double *__restrict__ state,
-                                                      int max_cells)
+                                                      int max_cells, int split)
 {
     __shared__ int off[PF_CELLS + 1];
     __shared__ double raw[PF_CELLS][PF_ROWS], quant[PF_CELLS][PF_ROWS];   // 9 of v_z, 9 of |v_perp|
     __shared__ QuantileTable qt;
     __shared__ int failed, bad;
     const Diode &dd = D[blockIdx.y];
-    const int c0 = blockIdx.x * PF_CELLS, tid = threadIdx.x;
+    const int group = (int)blockIdx.x / split, share = (int)blockIdx.x - group * split;
+    const int c0 = group * PF_CELLS, tid = threadIdx.x;
     const int q = blockIdx.z;
     const int s = q == 0 ? SP_P : SP_I;
     if (c0 >= dd.N) return;
@@ -1162,7 +1166,7 @@ __global__ __launch_bounds__(256) void k_profile_fill(const Diode *__restrict__ 
         __syncthreads();
     }
     const int end = off[PF_CELLS];
-    for (int i = off[0] + tid; i < end; i += 256) {
+    for (int i = off[0] + share * 256 + tid; i < end; i += 256 * split) {
         // the last cell that starts at or before slot i
         int cl = 0;
 #pragma unroll
@@ -2717,13 +2721,17 @@ extern "C" hipError_t picx_launch_load(const Diode *D, const long long *n_load, 
     return hipGetLastError();
 }
 
-// max_cells: the largest N over the diodes (row length of dens)
+// max_cells: the largest N over the diodes (row length of dens); per_cell: the
+// most particles per cell of a species that a diode was sized for
 extern "C" hipError_t picx_launch_profile_load(const Diode *D, const double *dens, int rows, int nd, int max_cells,
-                                               hipStream_t s)
+                                               int64_t per_cell, hipStream_t s)
 {
     hipLaunchKernelGGL(k_profile_count, dim3(nd), dim3(1024), 0, s, D, dens, rows, max_cells);
-    hipLaunchKernelGGL(k_profile_fill, dim3((max_cells + PF_CELLS - 1) / PF_CELLS, nd, 2), dim3(256), 0, s, D,
-                       rows == STATE_ROWS ? dens : nullptr, max_cells);
+    const int groups = (max_cells + PF_CELLS - 1) / PF_CELLS;
+    const int64_t rounds = std::max<int64_t>(1, PF_CELLS * per_cell / 256);    // of a block over its cells
+    const int split = (int)std::min<int64_t>(rounds, std::max<int64_t>(1, PF_BLOCKS / ((int64_t)groups * nd * 2)));
+    hipLaunchKernelGGL(k_profile_fill, dim3(groups * split, nd, 2), dim3(256), 0, s, D,
+                       rows == STATE_ROWS ? dens : nullptr, max_cells, split);
     hipLaunchKernelGGL(k_profile_clear, dim3(nd), dim3(256), 0, s, D);
     return hipGetLastError();
 }

@@ -507,3 +507,27 @@ def test_field_of_tiled_grids(torch, O, cells, electrons, ions):
         assert field_matches(O, cfg, h, oracle_from_gpu(O, cfg, st, t), 0, exact=True) == []
     assert restart_step_check(O, cfg, h, 2, exact_field=True) == []
     h.close()
+
+
+@pytest.mark.parametrize("cells,per_cell,diodes", [(2, 20000, 1), (8, 6000, 1), (17, 4000, 1), (5, 3000, 3), (130, 700, 1)])
+def test_state_load_of_few_cells_with_many_particles(torch, O, cells, per_cell, diodes):
+    """Where the cells are too few to fill the chip, several blocks share a
+    group's particles: every one is loaded once, as by the oracle."""
+    from paper_2605_07083_amd import pic
+    _say("case: state load, %d diodes of %d cells x %d" % (diodes, cells, per_cell))
+    cfgs = [presets.scaled(presets.tiny(), gamma_emit=1e21, N=cells, n_load=cells * per_cell // (d + 1), diode=d,
+                           capacity_factor=3.0) for d in range(diodes)]
+    sts = np.stack([_state(c, 60 + d) for d, c in enumerate(cfgs)])
+    h = pic.Handle(cfgs, state=torch.tensor(sts, dtype=torch.float64, device="cuda:0"))
+    for d, cfg in enumerate(cfgs):
+        g, t = gpu_state(h, d)
+        s = O.Sim(cfg)
+        s.load_state(sts[d])
+        for sp in (0, 2):
+            a, o = by_id(g[sp]), by_id(s.particles(sp))
+            assert np.array_equal(a["id"], o["id"]) and np.array_equal(a["z"], o["z"])
+            assert np.array_equal(a["tc"], o["tc"])
+            for c in ("vx", "vy", "vz"):
+                assert np.max(np.abs(a[c] - o[c].astype(np.float32)) / np.abs(o[c]).max()) < 1e-6
+        assert deposit_matches(O, cfg, h, g, d) == []
+    h.close()
